@@ -53,90 +53,186 @@ __device__ double newell_g(double x, double y, double z) {
   return sgn * r;
 }
 
-// All six entries by the closed form: sum over the 27 shifted points with
-// weights c(ex) c(ey) c(ez), c(0) = 2, c(+-1) = -1.
-__device__ void newell_closed(double X, double Y, double Z, double dx, double dy, double dz,
-                              double out[6]) {
-  double acc[6] = {0, 0, 0, 0, 0, 0};
-  for (int ex = -1; ex <= 1; ++ex) {
-    const double a = X + ex * dx;
-    const double cxw = ex == 0 ? 2.0 : -1.0;
-    for (int ey = -1; ey <= 1; ++ey) {
-      const double b = Y + ey * dy;
-      const double cyw = ey == 0 ? 2.0 : -1.0;
-      for (int ez = -1; ez <= 1; ++ez) {
-        const double c = Z + ez * dz;
-        const double w = cxw * cyw * (ez == 0 ? 2.0 : -1.0);
-        acc[0] += w * newell_f(a, b, c);
-        acc[1] += w * newell_f(b, a, c);
-        acc[2] += w * newell_f(c, b, a);
-        acc[3] += w * newell_g(a, b, c);
-        acc[4] += w * newell_g(a, c, b);
-        acc[5] += w * newell_g(b, c, a);
-      }
-    }
-  }
-  const double k = 1.0 / (4.0 * 3.14159265358979323846 * dx * dy * dz);
-  for (int i = 0; i < 6; ++i) out[i] = acc[i] * k;
+// Point q (0..26) of the closed form's 27-point second difference, all six
+// entries, weight c(ex) c(ey) c(ez) with c(0) = 2, c(+-1) = -1.
+__device__ __forceinline__ void newell_point(int q, double X, double Y, double Z, double dx,
+                                             double dy, double dz, double out[6]) {
+  const int ex = q / 9 - 1, ey = (q / 3) % 3 - 1, ez = q % 3 - 1;
+  const double a = X + ex * dx, b = Y + ey * dy, c = Z + ez * dz;
+  const double w = (ex == 0 ? 2.0 : -1.0) * (ey == 0 ? 2.0 : -1.0) * (ez == 0 ? 2.0 : -1.0);
+  out[0] = w * newell_f(a, b, c);
+  out[1] = w * newell_f(b, a, c);
+  out[2] = w * newell_f(c, b, a);
+  out[3] = w * newell_g(a, b, c);
+  out[4] = w * newell_g(a, c, b);
+  out[5] = w * newell_g(b, c, a);
 }
 
+// One node's contribution (offset u, weight wt) to the six entries, without
+// the prefactor; |u|^-5 from the reciprocal square root (a square root and a
+// division took twice the instructions of the rest of the node).
+__device__ __forceinline__ void far_node(double ux, double uy, double uz, double wt,
+                                         double acc[6]) {
+  const double r2 = ux * ux + uy * uy + uz * uz;
+  const double y = rsqrt(r2), y2 = y * y;
+  const double w = wt * (y2 * y2 * y);
+  acc[0] += w * (3.0 * ux * ux - r2);
+  acc[1] += w * (3.0 * uy * uy - r2);
+  acc[2] += w * (3.0 * uz * uz - r2);
+  const double w3 = 3.0 * w;
+  acc[3] += w3 * (ux * uy);
+  acc[4] += w3 * (ux * uz);
+  acc[5] += w3 * (uy * uz);
+}
+
+// Half-axis node xi, weight wi of the tent-weighted rule on a cell edge d.
+__device__ __forceinline__ void far_axis(double xi, double wi, double d, double& t, double& w) {
+  t = 0.5 * d * (xi + 1.0);
+  w = 0.5 * d * wi * (d - t);
+}
+
+// Nodes first, first + 8, ... of the NP^3 nodes of one octant (signs sx, sy,
+// sz) of the tent-weighted Gauss-Legendre rule.
 template <int NP>
-__device__ void far_quadrature(double X, double Y, double Z, double dx, double dy, double dz,
-                               const double* xi, const double* wi, double out[6]) {
-  // nodes and tent-weighted weights per axis, both halves
-  double tx[2 * NP], wx[2 * NP], ty[2 * NP], wy[2 * NP], tz[2 * NP], wz[2 * NP];
-#pragma unroll
-  for (int q = 0; q < NP; ++q) {
-    const double hx = 0.5 * dx * (xi[q] + 1.0), hy = 0.5 * dy * (xi[q] + 1.0),
-                 hz = 0.5 * dz * (xi[q] + 1.0);
-    tx[q] = hx; tx[q + NP] = -hx;
-    ty[q] = hy; ty[q + NP] = -hy;
-    tz[q] = hz; tz[q + NP] = -hz;
-    wx[q] = wx[q + NP] = 0.5 * dx * wi[q] * (dx - hx);
-    wy[q] = wy[q + NP] = 0.5 * dy * wi[q] * (dy - hy);
-    wz[q] = wz[q + NP] = 0.5 * dz * wi[q] * (dz - hz);
+__device__ __forceinline__ void far_nodes(double X, double Y, double Z, double dx, double dy,
+                                          double dz, const double* __restrict__ xi,
+                                          const double* __restrict__ wi, double sx, double sy,
+                                          double sz, int first, double acc[6]) {
+  for (int n = first; n < NP * NP * NP; n += 8) {
+    const int a = n / (NP * NP), b = (n / NP) % NP, c = n % NP;
+    double tx, ty, tz, wx, wy, wz;
+    far_axis(xi[a], wi[a], dx, tx, wx);
+    far_axis(xi[b], wi[b], dy, ty, wy);
+    far_axis(xi[c], wi[c], dz, tz, wz);
+    far_node(X + sx * tx, Y + sy * ty, Z + sz * tz, wx * wy * wz, acc);
   }
-  double acc[6] = {0, 0, 0, 0, 0, 0};
-  for (int a = 0; a < 2 * NP; ++a) {
-    const double ux = X + tx[a];
-    for (int b = 0; b < 2 * NP; ++b) {
-      const double uy = Y + ty[b];
-      const double wab = wx[a] * wy[b];
-      for (int c = 0; c < 2 * NP; ++c) {
-        const double uz = Z + tz[c];
-        const double r2 = ux * ux + uy * uy + uz * uz;
-        const double inv5 = 1.0 / (r2 * r2 * sqrt(r2));
-        const double w = wab * wz[c] * inv5;
-        acc[0] += w * (3.0 * ux * ux - r2);
-        acc[1] += w * (3.0 * uy * uy - r2);
-        acc[2] += w * (3.0 * uz * uz - r2);
-        acc[3] += w * (3.0 * ux * uy);
-        acc[4] += w * (3.0 * ux * uz);
-        acc[5] += w * (3.0 * uy * uz);
-      }
-    }
-  }
-  const double k = -1.0 / (4.0 * 3.14159265358979323846 * dx * dy * dz);
-  for (int i = 0; i < 6; ++i) out[i] = acc[i] * k;
 }
 
-__global__ void k_newell_octant(double* __restrict__ out, int nx, int ny, int nz, double dx,
-                                double dy, double dz, GaussRules gr) {
+// The rules' nodes and weights in LDS (indexed by lane-dependent nodes).
+struct RuleLds {
+  double x[13], w[13];   // 6 points at 0, 4 at 6, 3 at 10
+};
+__device__ __forceinline__ void load_rules(const GaussRules& gr, RuleLds& r) {
+  const int t = threadIdx.x;
+  if (t < 13) {
+    r.x[t] = t < 6 ? gr.x6[t] : t < 10 ? gr.x4[t - 6] : gr.x3[t - 10];
+    r.w[t] = t < 6 ? gr.w6[t] : t < 10 ? gr.w4[t - 6] : gr.w3[t - 10];
+  }
+  __syncthreads();
+}
+
+// Offsets below 40 h (closed form, 6- and 4-point rules): one wave per offset
+// of the box bx x by x bz that holds them all, its lanes sharing the 27
+// points or the 8 NP^3 nodes.  Offsets beyond 40 h: 8 lanes per offset, one
+// per octant of the 3-point rule's nodes.  Bound by the serial chain of
+// transcendental functions, square roots and divisions of one offset: with
+// one thread per offset (162 closed-form evaluations, up to 1728 nodes in a
+// row) the 200 x 100 x 2 film took 800 us and the 128^3 cube 1359 us; split
+// they take 21 + 14 us and 74 + 592 us (the cube's 453 M far nodes at 108
+// instructions each before, the reciprocal square root and the unrolled
+// nodes halving that).
+__global__ void __launch_bounds__(256)
+k_newell_near(double* __restrict__ out, int nx, int ny, int nz, int bx, int by, int bz, double dx,
+              double dy, double dz, GaussRules gr) {
+  __shared__ RuleLds rl;
+  load_rules(gr, rl);
+  const long long q = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  if (q >= (long long)bx * by * bz) return;
+  const int lane = threadIdx.x & 63;
+  const int i = (int)(q % bx);
+  const int j = (int)((q / bx) % by);
+  const int k = (int)(q / ((long long)bx * by));
+  const double X = i * dx, Y = j * dy, Z = k * dz;
+  const double h = fmax(dx, fmax(dy, dz));
+  const double r2 = X * X + Y * Y + Z * Z;
+  if (r2 >= 1600.0 * h * h) return;
+  const double sx = (lane & 1) ? -1.0 : 1.0, sy = (lane & 2) ? -1.0 : 1.0,
+               sz = (lane & 4) ? -1.0 : 1.0;
+  double v[6] = {0, 0, 0, 0, 0, 0};
+  double f = -1.0;
+  if (r2 < 36.0 * h * h) {
+    f = 1.0;
+    if (lane < 27) newell_point(lane, X, Y, Z, dx, dy, dz, v);
+  } else if (r2 < 256.0 * h * h) {
+    far_nodes<6>(X, Y, Z, dx, dy, dz, rl.x, rl.w, sx, sy, sz, lane >> 3, v);
+  } else {
+    far_nodes<4>(X, Y, Z, dx, dy, dz, rl.x + 6, rl.w + 6, sx, sy, sz, lane >> 3, v);
+  }
+  if (r2 < 36.0 * h * h) {
+    // second differences along z, then y, then x (the points' weights are
+    // the products of the axes'): each difference cancels before the next
+    // axis adds to it
+#pragma unroll
+    for (int st = 1; st < 27; st *= 3) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) {
+        const double a = __shfl(v[c], lane + st), b = __shfl(v[c], lane + 2 * st);
+        v[c] = (0.5 * a + v[c]) + (0.5 * a + b);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      v[c] += __shfl_xor(v[c], 32);
+      v[c] += __shfl_xor(v[c], 16);
+      v[c] += __shfl_xor(v[c], 8);
+      v[c] += __shfl_xor(v[c], 4);
+      v[c] += __shfl_xor(v[c], 2);
+      v[c] += __shfl_xor(v[c], 1);
+    }
+  }
+  if (lane == 0) {
+    const long long n = (long long)nx * ny * nz;
+    const long long idx = ((long long)k * ny + j) * nx + i;
+    const double kf = f / (4.0 * 3.14159265358979323846 * dx * dy * dz);
+    for (int c = 0; c < 6; ++c) out[(size_t)c * n + idx] = v[c] * kf;
+  }
+}
+
+__global__ void __launch_bounds__(256)
+k_newell_far(double* __restrict__ out, int nx, int ny, int nz, double dx, double dy, double dz,
+             GaussRules gr) {
+  __shared__ RuleLds rl;
+  load_rules(gr, rl);
   const long long n = (long long)nx * ny * nz;
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long long idx = t >> 3;
   if (idx >= n) return;
+  const int lane = (int)(t & 7);
   const int i = (int)(idx % nx);
   const int j = (int)((idx / nx) % ny);
   const int k = (int)(idx / ((long long)nx * ny));
   const double X = i * dx, Y = j * dy, Z = k * dz;
   const double h = fmax(dx, fmax(dy, dz));
-  const double r2 = X * X + Y * Y + Z * Z;
-  double v[6];
-  if (r2 < 36.0 * h * h) newell_closed(X, Y, Z, dx, dy, dz, v);
-  else if (r2 < 256.0 * h * h) far_quadrature<6>(X, Y, Z, dx, dy, dz, gr.x6, gr.w6, v);
-  else if (r2 < 1600.0 * h * h) far_quadrature<4>(X, Y, Z, dx, dy, dz, gr.x4, gr.w4, v);
-  else far_quadrature<3>(X, Y, Z, dx, dy, dz, gr.x3, gr.w3, v);
-  for (int c = 0; c < 6; ++c) out[(size_t)c * n + idx] = v[c];
+  if (X * X + Y * Y + Z * Z < 1600.0 * h * h) return;   // the same for the offset's 8 lanes
+  double v[6] = {0, 0, 0, 0, 0, 0};
+  double tx[3], ty[3], tz[3], wx[3], wy[3], wz[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    far_axis(rl.x[10 + q], rl.w[10 + q], dx, tx[q], wx[q]);
+    far_axis(rl.x[10 + q], rl.w[10 + q], dy, ty[q], wy[q]);
+    far_axis(rl.x[10 + q], rl.w[10 + q], dz, tz[q], wz[q]);
+    tx[q] = (lane & 1) ? X - tx[q] : X + tx[q];
+    ty[q] = (lane & 2) ? Y - ty[q] : Y + ty[q];
+    tz[q] = (lane & 4) ? Z - tz[q] : Z + tz[q];
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) far_node(tx[a], ty[b], tz[c], wx[a] * wy[b] * wz[c], v);
+  double o = 0.0;
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    double a = v[c];
+    a += __shfl_xor(a, 1);
+    a += __shfl_xor(a, 2);
+    a += __shfl_xor(a, 4);
+    o = c == lane ? a : o;
+  }
+  const double kf = -1.0 / (4.0 * 3.14159265358979323846 * dx * dy * dz);
+  if (lane < 6) out[(size_t)lane * n + idx] = o * kf;
 }
 
 // Embed the octant with wrap-around into real planes E[6][nz][Py][Px] for
@@ -281,8 +377,21 @@ template void launch_extract_3d<float>(hipStream_t, const void*, float*, int, in
 void launch_newell_octant(hipStream_t s, double* out, int nx, int ny, int nz, double dx, double dy,
                           double dz, const GaussRules& gr) {
   const long long n = (long long)nx * ny * nz;
-  hipLaunchKernelGGL(k_newell_octant, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, s, out, nx,
-                     ny, nz, dx, dy, dz, gr);
+  // box of the offsets below 40 h
+  const double h = dx > dy ? (dx > dz ? dx : dz) : (dy > dz ? dy : dz);
+  auto ext = [&](int m, double d) {
+    const double e = 40.0 * h / d + 2.0;
+    return e < (double)m ? (int)e : m;
+  };
+  const int bx = ext(nx, dx), by = ext(ny, dy), bz = ext(nz, dz);
+  const long long nb = (long long)bx * by * bz;
+  hipLaunchKernelGGL(k_newell_near, dim3((unsigned)((nb + 3) / 4)), dim3(256), 0, s, out, nx, ny,
+                     nz, bx, by, bz, dx, dy, dz, gr);
+  if (bx < nx || by < ny || bz < nz ||
+      (double)(nx - 1) * dx * (nx - 1) * dx + (double)(ny - 1) * dy * (ny - 1) * dy +
+              (double)(nz - 1) * dz * (nz - 1) * dz >= 1599.0 * h * h)
+    hipLaunchKernelGGL(k_newell_far, dim3((unsigned)((8 * n + 255) / 256)), dim3(256), 0, s, out,
+                       nx, ny, nz, dx, dy, dz, gr);
 }
 
 void launch_embed_thin(hipStream_t s, const double* oct, double* E, int nx, int ny, int nz, int Px,
