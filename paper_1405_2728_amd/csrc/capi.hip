@@ -383,7 +383,7 @@ int build_tensor(mm_ctx* c, Sample& s) {
   }
   launch_twiddles(st, twx64, s.Px, false);
   launch_twiddles(st, twy64, s.Py, false);
-  launch_newell_octant(st, oct, s.nx, s.ny, s.nz, s.dx, s.dy, s.dz, gr);
+  launch_newell_octant(st, oct, s.nx, s.ny, s.nz, s.dx, s.dy, s.dz, gr, single(c));
   launch_embed_thin(st, oct, E, s.nx, s.ny, s.nz, s.Px, s.Py);
   const int M = s.M;
   int R = 8192 / M;
@@ -438,7 +438,7 @@ int build_tensor3d(mm_ctx* c, Sample& s) {
   launch_twiddles(st, tw64[0], s.Px, false);
   launch_twiddles(st, tw64[1], s.Py, false);
   launch_twiddles(st, tw64[2], s.Pz, false);
-  launch_newell_octant(st, oct, s.nx, s.ny, s.nz, s.dx, s.dy, s.dz, gr);
+  launch_newell_octant(st, oct, s.nx, s.ny, s.nz, s.dx, s.dy, s.dz, gr, single(c));
   launch_embed_3d(st, oct, E, s.nx, s.ny, s.nz, s.Px, s.Py, s.Pz);
   const int M = s.M;
   int R = 8192 / M;

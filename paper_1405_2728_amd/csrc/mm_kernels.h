@@ -150,8 +150,9 @@ struct GaussRules {
 };
 
 // ---- tensor set-up (FP64) --------------------------------------------------
+// serial: every offset's sums in sequence (the single-precision form)
 void launch_newell_octant(hipStream_t s, double* out, int nx, int ny, int nz, double dx,
-                          double dy, double dz, const GaussRules& gr);
+                          double dy, double dz, const GaussRules& gr, bool serial);
 void launch_embed_thin(hipStream_t s, const double* oct, double* E, int nx, int ny, int nz, int Px,
                        int Py);
 template <typename T>

@@ -53,6 +53,96 @@ __device__ double newell_g(double x, double y, double z) {
   return sgn * r;
 }
 
+// All six entries by the closed form: sum over the 27 shifted points with
+// weights c(ex) c(ey) c(ez), c(0) = 2, c(+-1) = -1.
+__device__ void newell_closed(double X, double Y, double Z, double dx, double dy, double dz,
+                              double out[6]) {
+  double acc[6] = {0, 0, 0, 0, 0, 0};
+  for (int ex = -1; ex <= 1; ++ex) {
+    const double a = X + ex * dx;
+    const double cxw = ex == 0 ? 2.0 : -1.0;
+    for (int ey = -1; ey <= 1; ++ey) {
+      const double b = Y + ey * dy;
+      const double cyw = ey == 0 ? 2.0 : -1.0;
+      for (int ez = -1; ez <= 1; ++ez) {
+        const double c = Z + ez * dz;
+        const double w = cxw * cyw * (ez == 0 ? 2.0 : -1.0);
+        acc[0] += w * newell_f(a, b, c);
+        acc[1] += w * newell_f(b, a, c);
+        acc[2] += w * newell_f(c, b, a);
+        acc[3] += w * newell_g(a, b, c);
+        acc[4] += w * newell_g(a, c, b);
+        acc[5] += w * newell_g(b, c, a);
+      }
+    }
+  }
+  const double k = 1.0 / (4.0 * 3.14159265358979323846 * dx * dy * dz);
+  for (int i = 0; i < 6; ++i) out[i] = acc[i] * k;
+}
+
+template <int NP>
+__device__ void far_quadrature(double X, double Y, double Z, double dx, double dy, double dz,
+                               const double* xi, const double* wi, double out[6]) {
+  // nodes and tent-weighted weights per axis, both halves
+  double tx[2 * NP], wx[2 * NP], ty[2 * NP], wy[2 * NP], tz[2 * NP], wz[2 * NP];
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    const double hx = 0.5 * dx * (xi[q] + 1.0), hy = 0.5 * dy * (xi[q] + 1.0),
+                 hz = 0.5 * dz * (xi[q] + 1.0);
+    tx[q] = hx; tx[q + NP] = -hx;
+    ty[q] = hy; ty[q + NP] = -hy;
+    tz[q] = hz; tz[q + NP] = -hz;
+    wx[q] = wx[q + NP] = 0.5 * dx * wi[q] * (dx - hx);
+    wy[q] = wy[q + NP] = 0.5 * dy * wi[q] * (dy - hy);
+    wz[q] = wz[q + NP] = 0.5 * dz * wi[q] * (dz - hz);
+  }
+  double acc[6] = {0, 0, 0, 0, 0, 0};
+  for (int a = 0; a < 2 * NP; ++a) {
+    const double ux = X + tx[a];
+    for (int b = 0; b < 2 * NP; ++b) {
+      const double uy = Y + ty[b];
+      const double wab = wx[a] * wy[b];
+      for (int c = 0; c < 2 * NP; ++c) {
+        const double uz = Z + tz[c];
+        const double r2 = ux * ux + uy * uy + uz * uz;
+        const double inv5 = 1.0 / (r2 * r2 * sqrt(r2));
+        const double w = wab * wz[c] * inv5;
+        acc[0] += w * (3.0 * ux * ux - r2);
+        acc[1] += w * (3.0 * uy * uy - r2);
+        acc[2] += w * (3.0 * uz * uz - r2);
+        acc[3] += w * (3.0 * ux * uy);
+        acc[4] += w * (3.0 * ux * uz);
+        acc[5] += w * (3.0 * uy * uz);
+      }
+    }
+  }
+  const double k = -1.0 / (4.0 * 3.14159265358979323846 * dx * dy * dz);
+  for (int i = 0; i < 6; ++i) out[i] = acc[i] * k;
+}
+
+// One thread per offset, every sum in sequence: the single-precision form's
+// tensor.  Its iterates amplify the last bits of the tensor (a change of one
+// unit in the last place moves m by 1e-9 and a torque of 1e-5 Ms by 3e-4 of
+// itself within 31 updates), so that form keeps this order of summation.
+__global__ void k_newell_octant(double* __restrict__ out, int nx, int ny, int nz, double dx,
+                                double dy, double dz, GaussRules gr) {
+  const long long n = (long long)nx * ny * nz;
+  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= n) return;
+  const int i = (int)(idx % nx);
+  const int j = (int)((idx / nx) % ny);
+  const int k = (int)(idx / ((long long)nx * ny));
+  const double X = i * dx, Y = j * dy, Z = k * dz;
+  const double h = fmax(dx, fmax(dy, dz));
+  const double r2 = X * X + Y * Y + Z * Z;
+  double v[6];
+  if (r2 < 36.0 * h * h) newell_closed(X, Y, Z, dx, dy, dz, v);
+  else if (r2 < 256.0 * h * h) far_quadrature<6>(X, Y, Z, dx, dy, dz, gr.x6, gr.w6, v);
+  else if (r2 < 1600.0 * h * h) far_quadrature<4>(X, Y, Z, dx, dy, dz, gr.x4, gr.w4, v);
+  else far_quadrature<3>(X, Y, Z, dx, dy, dz, gr.x3, gr.w3, v);
+  for (int c = 0; c < 6; ++c) out[(size_t)c * n + idx] = v[c];
+}
+
 // Point q (0..26) of the closed form's 27-point second difference, all six
 // entries, weight c(ex) c(ey) c(ez) with c(0) = 2, c(+-1) = -1.
 __device__ __forceinline__ void newell_point(int q, double X, double Y, double Z, double dx,
@@ -375,8 +465,13 @@ template void launch_extract_3d<double>(hipStream_t, const void*, double*, int, 
 template void launch_extract_3d<float>(hipStream_t, const void*, float*, int, int, int, int);
 
 void launch_newell_octant(hipStream_t s, double* out, int nx, int ny, int nz, double dx, double dy,
-                          double dz, const GaussRules& gr) {
+                          double dz, const GaussRules& gr, bool serial) {
   const long long n = (long long)nx * ny * nz;
+  if (serial) {
+    hipLaunchKernelGGL(k_newell_octant, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, s, out,
+                       nx, ny, nz, dx, dy, dz, gr);
+    return;
+  }
   // box of the offsets below 40 h
   const double h = dx > dy ? (dx > dz ? dx : dz) : (dy > dz ? dy : dz);
   auto ext = [&](int m, double d) {
