@@ -726,6 +726,7 @@ struct BatchPlan {
   std::vector<PersistLaunch> px;          // x passes: one per rows per block R
   std::vector<PersistLaunch> pyz;         // yz pass: one per layer count
   PersistLaunch p3[3];                    // 3-D samples: y forward, z, y inverse
+  int max_rows = 0;                       // most per-block sums of a sample
   BatchDesc* descs = nullptr;
   BatchDesc* descs_ref = nullptr;         // reference pass (defect correction), or NULL
   WorkItem* items = nullptr;
@@ -803,6 +804,7 @@ int build_batch(mm_ctx* c, double* const* m, BatchPlan& P, const std::vector<cha
     b.hdref = corr ? s.hdref : nullptr;
     b.pass = corr ? 1 : 0;
     P.members.push_back(k);
+    P.max_rows = std::max(P.max_rows, s.nb3);
     d.push_back(b);
   }
   if (d.empty()) return MM_OK;
@@ -1083,7 +1085,7 @@ void enqueue_batched_iteration(mm_ctx* c, const BatchPlan& P) {
       x_pass(true);
     }
     Timer t(c, KID_FINISH);
-    launch_finish_batched(st, P.descs, (int)P.members.size());
+    launch_finish_batched(st, P.descs, (int)P.members.size(), P.max_rows);
     return;
   }
   {
@@ -1112,7 +1114,7 @@ void enqueue_batched_iteration(mm_ctx* c, const BatchPlan& P) {
   }
   {
     Timer t(c, KID_FINISH);
-    launch_finish_batched(st, P.descs, (int)P.members.size());
+    launch_finish_batched(st, P.descs, (int)P.members.size(), P.max_rows);
   }
 }
 

@@ -24,11 +24,57 @@ __global__ void __launch_bounds__(kFinishThreads) k_finish(const double* __restr
   finish_in_block<kFinishThreads, kFinishRows>(partials, nblocks, st, Ms, V, scratch);
 }
 
-// Batched: block b finishes sample b of the table.
+// Many per-block sums (large grids): a first stage in which block b sums
+// rows kFinishThreads b .. kFinishThreads (b + 1) - 1 in the fixed order of
+// block_reduce, writing one row per block to out; the one-block finish then
+// sums those.  Few rows are summed by the finish block directly.
+constexpr int kFinishDirect = 2048;
+
+__device__ __forceinline__ void stage1_rows(const double* __restrict__ partials, int nb,
+                                            double* __restrict__ out,
+                                            const MinState* __restrict__ st,
+                                            double (&scratch)[kNPartial * kFinishThreads / 64]) {
+  const int dn = st->done;   // read while the sums' loads are in flight
+  double v[kNPartial] = {};
+  const int r = blockIdx.x * kFinishThreads + threadIdx.x;
+  if (r < nb) {
+#pragma unroll
+    for (int q = 0; q < kNPartial; ++q) v[q] = partials[(size_t)r * kNPartial + q];
+  }
+  if (dn != 0) return;
+  bool is_max[kNPartial];
+  for (int q = 0; q < kNPartial; ++q) is_max[q] = q == kPartMax;
+  block_reduce<kFinishThreads>(v, is_max, scratch);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int q = 0; q < kNPartial; ++q) out[(size_t)blockIdx.x * kNPartial + q] = v[q];
+  }
+}
+
+__global__ void __launch_bounds__(kFinishThreads)
+k_finish_stage1(const double* __restrict__ partials, int nb, double* __restrict__ out,
+                const MinState* __restrict__ st) {
+  __shared__ double scratch[kNPartial * kFinishThreads / 64];
+  stage1_rows(partials, nb, out, st, scratch);
+}
+
+// Batched: the first stage of the samples that have one (blockIdx.y: sample),
+// then block b finishes sample b of the table, each in the per-sample order.
+__global__ void __launch_bounds__(kFinishThreads)
+k_finish_stage1_b(const BatchDesc* __restrict__ descs) {
+  __shared__ double scratch[kNPartial * kFinishThreads / 64];
+  const BatchDesc& d = descs[blockIdx.y];
+  if (d.nb3 <= kFinishDirect || (int)blockIdx.x * kFinishThreads >= d.nb3) return;
+  stage1_rows(d.partials, d.nb3, d.partials + (size_t)d.nb3 * kNPartial, d.st, scratch);
+}
+
 __global__ void __launch_bounds__(kFinishThreads) k_finish_b(const BatchDesc* __restrict__ descs) {
   __shared__ double scratch[kNPartial * kFinishThreads / 64];
   const BatchDesc& d = descs[blockIdx.x];
-  finish_in_block<kFinishThreads, kFinishRows>(d.partials, d.nb3, d.st, d.Ms, d.V, scratch);
+  const bool two = d.nb3 > kFinishDirect;
+  const int nb = two ? (d.nb3 + kFinishThreads - 1) / kFinishThreads : d.nb3;
+  finish_in_block<kFinishThreads, kFinishRows>(
+      two ? d.partials + (size_t)d.nb3 * kNPartial : d.partials, nb, d.st, d.Ms, d.V, scratch);
 }
 
 // Apply a pending midpoint update (eq. (7)) to m and store s = m+ - m.
@@ -225,33 +271,6 @@ void launch_set_mode(hipStream_t s, MinState* st, int mode) {
 
 int local_blocks(int N) { return (N + kLocalThreads - 1) / kLocalThreads; }
 
-// Many per-block sums (large grids): a first stage in which block b sums
-// rows kFinishThreads b .. kFinishThreads (b + 1) - 1 in the fixed order of
-// block_reduce, writing one row per block to out; the one-block finish then
-// sums those.  Few rows are summed by the finish block directly.
-constexpr int kFinishDirect = 2048;
-
-__global__ void __launch_bounds__(kFinishThreads)
-k_finish_stage1(const double* __restrict__ partials, int nb, double* __restrict__ out,
-                const MinState* __restrict__ st) {
-  __shared__ double scratch[kNPartial * kFinishThreads / 64];
-  const int dn = st->done;   // read while the sums' loads are in flight
-  double v[kNPartial] = {};
-  const int r = blockIdx.x * kFinishThreads + threadIdx.x;
-  if (r < nb) {
-#pragma unroll
-    for (int q = 0; q < kNPartial; ++q) v[q] = partials[(size_t)r * kNPartial + q];
-  }
-  if (dn != 0) return;
-  bool is_max[kNPartial];
-  for (int q = 0; q < kNPartial; ++q) is_max[q] = q == kPartMax;
-  block_reduce<kFinishThreads>(v, is_max, scratch);
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int q = 0; q < kNPartial; ++q) out[(size_t)blockIdx.x * kNPartial + q] = v[q];
-  }
-}
-
 int finish_single_stage_max() { return kFinishDirect; }
 
 int finish_extra_rows(int nblocks) {
@@ -272,7 +291,10 @@ void launch_finish(hipStream_t s, double* partials, int nblocks, MinState* st, d
   hipLaunchKernelGGL(k_finish, dim3(1), dim3(kFinishThreads), 0, s, partials, nblocks, st, Ms, V);
 }
 
-void launch_finish_batched(hipStream_t s, const BatchDesc* descs, int n_samples) {
+void launch_finish_batched(hipStream_t s, const BatchDesc* descs, int n_samples, int max_rows) {
+  if (max_rows > kFinishDirect)
+    hipLaunchKernelGGL(k_finish_stage1_b, dim3(finish_extra_rows(max_rows), n_samples),
+                       dim3(kFinishThreads), 0, s, descs);
   hipLaunchKernelGGL(k_finish_b, dim3(n_samples), dim3(kFinishThreads), 0, s, descs);
 }
 

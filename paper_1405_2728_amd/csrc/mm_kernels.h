@@ -214,7 +214,8 @@ void launch_x_batched(hipStream_t s, bool inverse, const BatchDesc* descs, const
 template <typename T>
 void launch_yz_batched(hipStream_t s, const BatchDesc* descs, const WorkItem* items, int n_items,
                        int Py, int nz, int tstride);
-void launch_finish_batched(hipStream_t s, const BatchDesc* descs, int n_samples);
+// max_rows: the largest number of per-block sums of a sample
+void launch_finish_batched(hipStream_t s, const BatchDesc* descs, int n_samples, int max_rows);
 // persistent batched passes: one launch covers the items of every sample,
 // whatever its transform length (x: items of samples with R <= threads / 192;
 // yz: samples with nz layers); grid: blocks resident together (a multiple of
