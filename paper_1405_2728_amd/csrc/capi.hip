@@ -565,10 +565,10 @@ void enqueue_demag_mid(mm_ctx* c, const Sample& s, const Conv& v, const int* don
       Timer t(c, KID_Z3);
       if (v.sp)
         launch_z3<float>(st, v.B, s.nz, s.Py, s.Pz, s.M, (const float*)v.Tt, v.tstride,
-                         (float)scale, v.twz, done);
+                         (float)scale, v.twz, done, false);
       else
         launch_z3<double>(st, v.B, s.nz, s.Py, s.Pz, s.M, (const double*)v.Tt, v.tstride, scale,
-                          v.twz, done);
+                          v.twz, done, !single(c));
     }
     {
       Timer t(c, KID_Y3I);
@@ -915,19 +915,19 @@ int build_batch(mm_ctx* c, double* const* m, BatchPlan& P, const std::vector<cha
     std::vector<WorkItem> v;
     for (int i = 0; i < (int)d.size(); ++i) {
       if (!d[i].B) continue;
-      const int nb = st == 1 ? z3_blocks(d[i].Py, d[i].M) : y3_blocks(d[i].nz, d[i].M);
+      const int nb = st == 1 ? z3_blocks(d[i].Py, d[i].Pz, d[i].M, !sp) : y3_blocks(d[i].nz, d[i].M);
       for (int blk = 0; blk < nb; ++blk) v.push_back({i, blk});
       const int len = st == 1 ? d[i].Pz : d[i].Py;
-      L.lds = std::max(L.lds, w3_block_lds(sp, len));
-      L.lds_ref = std::max(L.lds_ref, w3_block_lds(false, len));
+      L.lds = std::max(L.lds, w3_block_lds(sp, st - 1, len, !sp));
+      L.lds_ref = std::max(L.lds_ref, w3_block_lds(false, st - 1, len, false));
     }
     if (v.empty()) continue;
     xcd_order(v);
     L.off = (int)all.size();
     L.n = (int)v.size();
     all.insert(all.end(), v.begin(), v.end());
-    L.grid = w3_persistent_grid(sp, st - 1, L.lds);
-    if (refine) L.grid_ref = w3_persistent_grid(false, st - 1, L.lds_ref);
+    L.grid = w3_persistent_grid(sp, st - 1, L.lds, !sp);
+    if (refine) L.grid_ref = w3_persistent_grid(false, st - 1, L.lds_ref, false);
   }
   if (hipMalloc((void**)&P.descs, d.size() * sizeof(BatchDesc)) != hipSuccess ||
       (refine && hipMalloc((void**)&P.descs_ref, d.size() * sizeof(BatchDesc)) != hipSuccess) ||
@@ -1013,7 +1013,7 @@ void enqueue_batched_reference(mm_ctx* c, const BatchPlan& P) {
           if (i == (int)P.pyz.size()) {
             for (int q = 0; q < 3; ++q)
               launch_3d_persistent<double>(st, q - 1, P.descs_ref, P.items + P.p3[q].off,
-                                           P.p3[q].n, P.p3[q].lds_ref, P.p3[q].grid_ref);
+                                           P.p3[q].n, P.p3[q].lds_ref, P.p3[q].grid_ref, false);
             return;
           }
           const PersistLaunch& L = P.pyz[i];
@@ -1068,8 +1068,8 @@ void enqueue_batched_iteration(mm_ctx* c, const BatchPlan& P) {
         if (i == (int)P.pyz.size()) {
           for (int q = 0; q < 3; ++q) {
             const PersistLaunch& L = P.p3[q];
-            if (sp) launch_3d_persistent<float>(s, q - 1, P.descs, P.items + L.off, L.n, L.lds, L.grid);
-            else launch_3d_persistent<double>(s, q - 1, P.descs, P.items + L.off, L.n, L.lds, L.grid);
+            if (sp) launch_3d_persistent<float>(s, q - 1, P.descs, P.items + L.off, L.n, L.lds, L.grid, false);
+            else launch_3d_persistent<double>(s, q - 1, P.descs, P.items + L.off, L.n, L.lds, L.grid, true);
           }
           return;
         }

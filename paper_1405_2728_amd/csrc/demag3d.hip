@@ -213,6 +213,107 @@ __device__ __forceinline__ void z3_body(cx<T>* __restrict__ B, int nz, int Py,
   }
 }
 
+// Pencils per wave of the packed z pass (double precision, 64 and 128
+// points).  The 8-point stages of a 64 VL-point transform use 8 VL lanes, so
+// one short pencil per wave leaves most lanes idle in most of the work; PK
+// packed pencils keep 8 PK VL lanes busy at the registers of a 64 PK VL-point
+// transform.  One pencil -> packed: 100 x 75 x 20 (64 points) 111 -> 39 us,
+// 37 x 29 x 11 25 -> 12, 200 x 200 x 40 (128 points) 519 -> 334, 64^3 39 -> 30.
+// At 128 points 4 pencils (256 VGPRs, 2 waves per SIMD instead of 3) took 36
+// where 2 take 30 (48^3), and at 256 points 2 pencils 241 us where 1 takes 205
+// (128^3), so longer pencils stay unpacked.
+__host__ __device__ constexpr int z3_pack(int Pz) { return Pz == 64 ? 8 : Pz == 128 ? 2 : 1; }
+
+// Logical block L of the packed z pass: wave w takes PK consecutive pencils
+// (kx, ky .. ky + PK - 1); otherwise z3_body.
+template <int VL>
+__device__ __forceinline__ void z3_pk_body(cx<double>* __restrict__ B, int nz, int Py,
+                                           const double* __restrict__ T3, int rstride,
+                                           double scale, const cx<double>* __restrict__ twz,
+                                           const int* __restrict__ done, int L) {
+  using T = double;
+  if (done != nullptr && *done != 0) return;
+  constexpr int n = 64 * VL;
+  constexpr int PK = z3_pack(n);
+  constexpr int NB = PK * VL == 8 ? 1 : 2;         // input buffers: the next component's loads ahead
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = thread_index();
+  const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: pencil addresses in SGPRs
+  const int pen = (L * kZ3Waves + w) * PK;    // pencil index kx * Py + ky
+  cx<T>* tbuf = reinterpret_cast<cx<T>*>(smem) + w * (PK * VL * 72);
+  cx<T>* P = B + (size_t)pen * nz * 3;
+  cx<T> F[3][8];
+  cx<T> xin[NB][PK][VL];
+  auto load = [&](int c, cx<T> (&x)[PK][VL]) {
+#pragma unroll
+    for (int p = 0; p < PK; ++p)
+#pragma unroll
+      for (int r = 0; r < VL; ++r) {
+        const int z = lane + 64 * r;
+        x[p][r] = z < nz ? (P + (size_t)p * nz * 3 + c)[(unsigned)z * 3u] : mk(T(0), T(0));
+      }
+  };
+  load(0, xin[0]);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    if (NB == 2 && c < 2) load(c + 1, xin[(c + 1) % NB]);
+    wfft_forward_pk<T, VL, PK>(xin[c % NB], F[c], tbuf, reload(twz), lane);
+    __builtin_amdgcn_sched_barrier(0);
+    if (NB == 1 && c < 2) load(c + 1, xin[0]);
+  }
+  const int hy = Py >> 1;
+  const int k = lane >> 3;
+  const int kx = pen / Py;
+  const int ky = pen - kx * Py + (PK > 1 ? k / VL : 0);      // Py is a multiple of PK: the same kx
+  const bool ny_neg = ky > hy;
+  const int kyp = ny_neg ? Py - ky : ky;
+  const T sy = ny_neg ? T(-1) : T(1);
+  const T* trow = T3 + ((size_t)kx * (hy + 1) + kyp) * rstride;
+  if (PK * VL == 8 || lane < 8 * PK * VL) {
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+      const int kz = k % VL + VL * ((lane & 7) + 8 * d);
+      const bool nz_neg = kz > n / 2;
+      const int kzp = nz_neg ? n - kz : kz;
+      const T sz = nz_neg ? T(-1) : T(1);
+      const T* t = trow + kzp * 6;
+      const T xx = t[0], yy = t[1], zz = t[2];
+      const T xy = t[3] * sy, xz = t[4] * sz, yz = t[5] * (sy * sz);
+      const cx<T> fx = F[0][d], fy = F[1][d], fz = F[2][d];
+      F[0][d] = scl(add(add(scl(fx, xx), scl(fy, xy)), scl(fz, xz)), scale);
+      F[1][d] = scl(add(add(scl(fx, xy), scl(fy, yy)), scl(fz, yz)), scale);
+      F[2][d] = scl(add(add(scl(fx, xz), scl(fy, yz)), scl(fz, zz)), scale);
+      // the scaling is not contracted into the inverse transform: 154
+      // instead of 252 VGPRs (64 points)
+      opaque(F[0][d]);
+      opaque(F[1][d]);
+      opaque(F[2][d]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    cx<T> xo[PK][VL];
+    wfft_inverse_pk<T, VL, PK>(F[c], xo, tbuf, reload(twz), lane);
+#pragma unroll
+    for (int p = 0; p < PK; ++p)
+#pragma unroll
+      for (int r = 0; r < VL; ++r) {
+        const int z = lane + 64 * r;
+        if (z < nz) (P + (size_t)p * nz * 3 + c)[(unsigned)z * 3u] = xo[p][r];
+      }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+template <int VL>
+__global__ void __launch_bounds__(64 * kZ3Waves, 3)
+k_z3_pk(cx<double>* __restrict__ B, int nz, int Py, const double* __restrict__ T3, int rstride,
+        double scale, const cx<double>* __restrict__ twz, const int* __restrict__ done) {
+  z3_pk_body<VL>(B, nz, Py, T3, rstride, scale, twz, done, xcd_remap(blockIdx.x, gridDim.x));
+}
+
 // FP64 up to 256 points: compiled for 3 resident waves per SIMD (168
 // VGPRs, no spill; 170 and 2 waves otherwise)
 template <typename T, int VL, bool HALF>
@@ -229,7 +330,8 @@ k_z3(cx<T>* __restrict__ B, int nz, int Py, const T* __restrict__ T3, int rstrid
 // XCD-ordered table (persist_loop), a branch on the item's length.
 static_assert(kY3Waves == kZ3Waves, "the 3-D stages share one block size");
 
-template <typename T, int VL>
+// PACK: the z stage packs its short pencils (double-precision contexts).
+template <typename T, int VL, bool PACK>
 __device__ __forceinline__ void w3_item(int stage, const BatchDesc& d, int L) {
   constexpr bool HALF = k3dHalf;
   const int nzb = (d.nz + kY3Waves - 1) / kY3Waves;
@@ -239,22 +341,25 @@ __device__ __forceinline__ void w3_item(int stage, const BatchDesc& d, int L) {
   else if (stage > 0)
     y3_inv_body<T, VL, HALF>((cx<T>*)d.spec, (const cx<T>*)d.B, d.nz, d.ny, nzb, d.M,
                              (const cx<T>*)d.twy, &d.st->done, L);
+  else if constexpr (PACK && z3_pack(64 * VL) > 1)
+    z3_pk_body<VL>((cx<double>*)d.B, d.nz, d.Py, (const double*)d.Tt, d.tstride, d.scale,
+                   (const cx<double>*)d.twz, &d.st->done, L);
   else
     z3_body<T, VL, HALF>((cx<T>*)d.B, d.nz, d.Py, (const T*)d.Tt, d.tstride, (T)d.scale,
                          (const cx<T>*)d.twz, &d.st->done, L);
 }
 
-template <typename T, int STAGE>
+template <typename T, int STAGE, bool PACK>
 __global__ void __launch_bounds__(64 * kY3Waves)
 k_w3_p(const BatchDesc* __restrict__ descs, const WorkItem* __restrict__ items, int n_items) {
   persist_loop(n_items, [&](int v) {
     const WorkItem it = items[v];
     const BatchDesc& d = descs[it.sample];
     switch ((STAGE == 0 ? d.Pz : d.Py) >> 6) {
-      case 1: w3_item<T, 1>(STAGE, d, it.block); break;
-      case 2: w3_item<T, 2>(STAGE, d, it.block); break;
-      case 4: w3_item<T, 4>(STAGE, d, it.block); break;
-      case 8: w3_item<T, 8>(STAGE, d, it.block); break;
+      case 1: w3_item<T, 1, PACK>(STAGE, d, it.block); break;
+      case 2: w3_item<T, 2, PACK>(STAGE, d, it.block); break;
+      case 4: w3_item<T, 4, PACK>(STAGE, d, it.block); break;
+      case 8: w3_item<T, 8, PACK>(STAGE, d, it.block); break;
       default: break;
     }
   });
@@ -299,6 +404,15 @@ void launch_y3(hipStream_t s, void* A, void* B, int nz, int ny, int Py, int M, i
   }
 }
 
+int z3_blocks(int Py, int Pz, int M, bool pack) {
+  return (M + 1) * (Py / (kZ3Waves * (pack ? z3_pack(Pz) : 1)));
+}
+
+// LDS of a packed z block: 72 elements per group of 8 lanes and wave
+static size_t z3_pk_lds(int Pz) {
+  return (size_t)kZ3Waves * z3_pack(Pz) * (Pz / 64) * 72 * sizeof(cx<double>);
+}
+
 template <typename T, int VL>
 static void z3_dispatch(hipStream_t s, void* B, int nz, int Py, int M, const T* T3, int rstride,
                         T scale, const void* twz, const int* done) {
@@ -312,9 +426,31 @@ static void z3_dispatch(hipStream_t s, void* B, int nz, int Py, int M, const T* 
                      (const cx<T>*)twz, done);
 }
 
+template <int VL>
+static void z3_pk_dispatch(hipStream_t s, void* B, int nz, int Py, int M, const double* T3,
+                           int rstride, double scale, const void* twz, const int* done) {
+  const size_t lds = z3_pk_lds(64 * VL);
+  // Py is a multiple of kZ3Waves PK (32 at most), so every wave owns PK pencils
+  const dim3 grid((unsigned)z3_blocks(Py, 64 * VL, M, true));
+  auto k = k_z3_pk<VL>;
+  set_lds(k, lds);
+  hipLaunchKernelGGL(k, grid, dim3(64 * kZ3Waves), lds, s, (cx<double>*)B, nz, Py, T3, rstride,
+                     scale, (const cx<double>*)twz, done);
+}
+
 template <typename T>
 void launch_z3(hipStream_t s, void* B, int nz, int Py, int Pz, int M, const T* T3, int rstride,
-               T scale, const void* twz, const int* done) {
+               T scale, const void* twz, const int* done, bool pack) {
+  if constexpr (sizeof(T) == 8) {
+    if (pack && Pz == 64) {
+      z3_pk_dispatch<1>(s, B, nz, Py, M, T3, rstride, scale, twz, done);
+      return;
+    }
+    if (pack && Pz == 128) {
+      z3_pk_dispatch<2>(s, B, nz, Py, M, T3, rstride, scale, twz, done);
+      return;
+    }
+  }
   switch (Pz) {
     case 64: z3_dispatch<T, 1>(s, B, nz, Py, M, T3, rstride, scale, twz, done); break;
     case 128: z3_dispatch<T, 2>(s, B, nz, Py, M, T3, rstride, scale, twz, done); break;
@@ -324,7 +460,6 @@ void launch_z3(hipStream_t s, void* B, int nz, int Py, int Pz, int M, const T* T
 }
 
 int y3_blocks(int nz, int M) { return (M + 1) * ((nz + kY3Waves - 1) / kY3Waves); }
-int z3_blocks(int Py, int M) { return (M + 1) * (Py / kZ3Waves); }
 
 template <typename T, int VL>
 static size_t w3_lds() {
@@ -332,7 +467,8 @@ static size_t w3_lds() {
   return (size_t)kY3Waves * wfft_buf<VL, HALF>() * sizeof(cx<T>);
 }
 
-size_t w3_block_lds(bool single, int P) {
+size_t w3_block_lds(bool single, int stage, int P, bool pack) {
+  if (stage == 0 && pack) return z3_pk_lds(P);
   switch (P) {
     case 64: return single ? w3_lds<float, 1>() : w3_lds<double, 1>();
     case 128: return single ? w3_lds<float, 2>() : w3_lds<double, 2>();
@@ -342,13 +478,16 @@ size_t w3_block_lds(bool single, int P) {
 }
 
 template <typename T>
-static const void* w3_kernel(int stage) {
-  return stage < 0 ? (const void*)k_w3_p<T, -1>
-                   : (stage > 0 ? (const void*)k_w3_p<T, 1> : (const void*)k_w3_p<T, 0>);
+static const void* w3_kernel(int stage, bool pack) {
+  if (stage < 0) return (const void*)k_w3_p<T, -1, false>;
+  if (stage > 0) return (const void*)k_w3_p<T, 1, false>;
+  if constexpr (sizeof(T) == 8)
+    if (pack) return (const void*)k_w3_p<T, 0, true>;
+  return (const void*)k_w3_p<T, 0, false>;
 }
 
-int w3_persistent_grid(bool single, int stage, size_t lds) {
-  const void* k = single ? w3_kernel<float>(stage) : w3_kernel<double>(stage);
+int w3_persistent_grid(bool single, int stage, size_t lds, bool pack) {
+  const void* k = single ? w3_kernel<float>(stage, false) : w3_kernel<double>(stage, pack);
   if (lds > 48 * 1024) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   int per_cu = 0, dev = 0, cus = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 64 * kY3Waves, lds) != hipSuccess ||
@@ -363,26 +502,26 @@ int w3_persistent_grid(bool single, int stage, size_t lds) {
 
 template <typename T>
 void launch_3d_persistent(hipStream_t s, int stage, const BatchDesc* descs, const WorkItem* items,
-                          int n_items, size_t lds, int grid) {
+                          int n_items, size_t lds, int grid, bool pack) {
   const int g = n_items < grid ? n_items : grid;
   if (g <= 0) return;
-  const void* k = w3_kernel<T>(stage);
+  const void* k = w3_kernel<T>(stage, pack);
   if (lds > 48 * 1024) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   void* args[] = {(void*)&descs, (void*)&items, (void*)&n_items};
   (void)hipLaunchKernel(k, dim3(g), dim3(64 * kY3Waves), args, lds, s);
 }
 
 template void launch_3d_persistent<double>(hipStream_t, int, const BatchDesc*, const WorkItem*, int,
-                                           size_t, int);
+                                           size_t, int, bool);
 template void launch_3d_persistent<float>(hipStream_t, int, const BatchDesc*, const WorkItem*, int,
-                                          size_t, int);
+                                          size_t, int, bool);
 template void launch_y3<double>(hipStream_t, void*, void*, int, int, int, int, int, const void*,
                                 const int*);
 template void launch_y3<float>(hipStream_t, void*, void*, int, int, int, int, int, const void*,
                                const int*);
 template void launch_z3<double>(hipStream_t, void*, int, int, int, int, const double*, int, double,
-                                const void*, const int*);
+                                const void*, const int*, bool);
 template void launch_z3<float>(hipStream_t, void*, int, int, int, int, const float*, int, float,
-                               const void*, const int*);
+                               const void*, const int*, bool);
 
 }  // namespace mmk

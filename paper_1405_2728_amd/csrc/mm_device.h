@@ -34,6 +34,15 @@ __device__ __forceinline__ int thread_index() {
   return t;
 }
 
+// The pointer through an empty asm statement: loads through the result are
+// not merged with, or held in registers from, earlier ones (twiddles that
+// would otherwise stay live over a whole pass).
+template <typename P>
+__device__ __forceinline__ P* reload(P* p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 template <typename T>
 struct alignas(2 * sizeof(T)) cx {
   T x, y;
@@ -57,6 +66,13 @@ __device__ __forceinline__ cx<T> conj(cx<T> a) { return mk(a.x, -a.y); }
 template <int DIR, typename T>
 __device__ __forceinline__ cx<T> rot90(cx<T> a) {
   return DIR < 0 ? mk(a.y, -a.x) : mk(-a.y, a.x);
+}
+
+// v through an empty asm statement: no arithmetic before it is contracted
+// (fused multiply-add) with any after it.
+template <typename T>
+__device__ __forceinline__ void opaque(cx<T>& v) {
+  asm volatile("" : "+v"(v.x), "+v"(v.y));
 }
 
 // ---------------------------------------------------------------------------

@@ -177,9 +177,12 @@ template <typename T>
 void launch_y3(hipStream_t s, void* A, void* B, int nz, int ny, int Py, int M, int dir,
                const void* twy, const int* done);
 // z transform of every (kx, ky) pencil of B, product with the tensor, inverse.
+// pack: short pencils share a wave (double-precision contexts; the passes of
+// a single-precision context, whose iterates amplify a last bit contracted
+// otherwise, keep one pencil per wave in both precisions)
 template <typename T>
 void launch_z3(hipStream_t s, void* B, int nz, int Py, int Pz, int M, const T* T3, int rstride,
-               T scale, const void* twz, const int* done);
+               T scale, const void* twz, const int* done, bool pack);
 // padded y and z lengths handled by the 3-D kernels (powers of two, 64..512)
 inline bool full3d_len_ok(int P) { return P == 64 || P == 128 || P == 256 || P == 512; }
 
@@ -227,14 +230,14 @@ void launch_x_persistent(hipStream_t s, bool inverse, const BatchDesc* descs,
                          const WorkItem* items, int n_items, int threads, size_t lds, int grid);
 // 3-D path (demag3d.hip), persistent batched: stage -1 forward y, 0 z with
 // the tensor product, +1 inverse y; items = (sample, block of the stage's
-// per-sample grid: (M+1) ceil(nz/4) for y, (M+1) Py/4 for z)
-int w3_persistent_grid(bool single, int stage, size_t lds);
-size_t w3_block_lds(bool single, int P);
+// per-sample grid: (M+1) ceil(nz/4) for y, z3_blocks for z)
+int w3_persistent_grid(bool single, int stage, size_t lds, bool pack);
+size_t w3_block_lds(bool single, int stage, int P, bool pack);
 int y3_blocks(int nz, int M);
-int z3_blocks(int Py, int M);
+int z3_blocks(int Py, int Pz, int M, bool pack);
 template <typename T>
 void launch_3d_persistent(hipStream_t s, int stage, const BatchDesc* descs, const WorkItem* items,
-                          int n_items, size_t lds, int grid);
+                          int n_items, size_t lds, int grid, bool pack);
 int yz_persistent_grid(bool single, int nz, size_t lds);
 size_t yz_block_lds(bool single, int Py, int nz, int tstride);
 template <typename T>

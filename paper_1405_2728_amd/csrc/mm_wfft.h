@@ -142,6 +142,94 @@ __device__ __forceinline__ void wfft_inverse(cx<T> (&u)[8], cx<T> (&v)[VL], cx<T
   dft_small<VL, 1>(v);
 }
 
+// Packed forms: PK sequences of length 64 VL per wave (PK VL <= 8), lane l
+// holding x_p[l + 64 r] in v[p][r].  Group k = p VL + k1 of 8 lanes takes the
+// place of k1 above, so that short lengths keep 8 PK VL lanes busy in the
+// 8-point stages instead of 8 VL; every sequence sees the same operations.
+// Transpose buffer: 72 PK VL elements.
+template <typename T, int VL, int PK, int TS = 1>
+__device__ __forceinline__ void wfft_forward_pk(cx<T> (&v)[PK][VL], cx<T> (&u)[8], cx<T>* lds,
+                                                const cx<T>* __restrict__ tw, int lane) {
+  constexpr int NG = 8 * VL * PK;
+  static_assert(NG <= 64, "more groups than lanes");
+#pragma unroll
+  for (int p = 0; p < PK; ++p) dft_small<VL, -1>(v[p]);
+#pragma unroll
+  for (int k1 = 1; k1 < VL; ++k1) {
+    const cx<T> w = tw[TS * lane * k1];
+#pragma unroll
+    for (int p = 0; p < PK; ++p) v[p][k1] = mul(v[p][k1], w);
+  }
+  const int k = lane >> 3, a = lane & 7;
+#pragma unroll
+  for (int p = 0; p < PK; ++p)
+#pragma unroll
+    for (int k1 = 0; k1 < VL; ++k1) lds[wf_f1(p * VL + k1, lane)] = v[p][k1];
+  __builtin_amdgcn_wave_barrier();
+  if (lane < NG) {
+#pragma unroll
+    for (int b = 0; b < 8; ++b) u[b] = lds[wf_f1(k, a + 8 * b)];
+    dft8<-1>(u);
+#pragma unroll
+    for (int c = 1; c < 8; ++c) u[c] = mul(u[c], tw[TS * a * c * VL]);
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (lane < NG) {
+#pragma unroll
+    for (int cc = 0; cc < 8; ++cc) lds[wf_f2(k, cc, a)] = u[cc];
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (lane < NG) {
+#pragma unroll
+    for (int aa = 0; aa < 8; ++aa) u[aa] = lds[wf_f2(k, a, aa)];
+    dft8<-1>(u);
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
+template <typename T, int VL, int PK, int TS = 1>
+__device__ __forceinline__ void wfft_inverse_pk(cx<T> (&u)[8], cx<T> (&v)[PK][VL], cx<T>* lds,
+                                                const cx<T>* __restrict__ tw, int lane) {
+  constexpr int NG = 8 * VL * PK;
+  static_assert(NG <= 64, "more groups than lanes");
+  const int k = lane >> 3, a = lane & 7;
+  if (lane < NG) {
+    dft8<1>(u);
+#pragma unroll
+    for (int aa = 0; aa < 8; ++aa) lds[wf_f2(k, a, aa)] = u[aa];
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (lane < NG) {
+#pragma unroll
+    for (int cc = 0; cc < 8; ++cc) u[cc] = lds[wf_f2(k, cc, a)];
+#pragma unroll
+    for (int cc = 1; cc < 8; ++cc) u[cc] = mul(u[cc], conj(tw[TS * a * cc * VL]));
+    dft8<1>(u);
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (lane < NG) {
+#pragma unroll
+    for (int b = 0; b < 8; ++b) lds[wf_f1(k, a + 8 * b)] = u[b];
+  }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int p = 0; p < PK; ++p)
+#pragma unroll
+    for (int kk = 0; kk < VL; ++kk) {
+      const cx<T>& e = lds[wf_f1(p * VL + kk, lane)];
+      v[p][kk] = mk(e.x, e.y);
+    }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int kk = 1; kk < VL; ++kk) {
+    const cx<T> w = conj(tw[TS * lane * kk]);
+#pragma unroll
+    for (int p = 0; p < PK; ++p) v[p][kk] = mul(v[p][kk], w);
+  }
+#pragma unroll
+  for (int p = 0; p < PK; ++p) dft_small<VL, 1>(v[p]);
+}
+
 // Frequency index held in slot d by lane g of the permuted distribution.
 template <int VL>
 __device__ __forceinline__ int wfft_freq(int lane, int d) {
