@@ -190,6 +190,14 @@ int pad_wave(int n, int unit, bool mr) {
 }
 int pad_x(int nx, bool mr) { return nx < 2 ? 2 : pad_wave(2 * nx - 1, 128, mr); }
 int pad_thin_y(int ny, bool mr) { return pad_wave(2 * ny - 1, 64, mr); }
+// Lengths of the double-precision contexts beyond the wave FFT's 512 points:
+// the long wave FFT takes 64 VL points, VL = 10, 12, 14, 16, where the power
+// of two would be 1024 (the grids accepted are those of the powers of two).
+int pad_long(int n, int p, bool mr) {
+  if (p != 1024 || !mr) return p;
+  const int w = (n + 127) / 128 * 128;
+  return w < p ? w : p;
+}
 int pad_3d(int n) {
   const int p = next_pow2(2 * n - 1);
   return p < 64 ? 64 : p;
@@ -580,10 +588,10 @@ void enqueue_demag_mid(mm_ctx* c, const Sample& s, const Conv& v, const int* don
     const double scale = -s.Ms / ((double)s.M * (double)s.Py);
     if (v.sp)
       launch_yz_thin<float>(st, v.spec, s.nz, s.ny, s.Py, s.M, (const float*)v.Tt, v.tstride,
-                            (float)scale, v.twy, done, v.yz_var);
+                            (float)scale, v.twy, done, v.yz_var, false);
     else
       launch_yz_thin<double>(st, v.spec, s.nz, s.ny, s.Py, s.M, (const double*)v.Tt, v.tstride,
-                             scale, v.twy, done, v.yz_var);
+                             scale, v.twy, done, v.yz_var, !single(c));
   }
   c->prof = prof;
 }
@@ -1266,10 +1274,10 @@ int time_yz(mm_ctx* c, Sample& s, int var, double* us) {
   auto pass = [&]() {
     if (sp)
       launch_yz_thin<float>(st, s.spec, s.nz, s.ny, s.Py, s.M, (const float*)s.Tt, s.tstride,
-                            -1.0f, s.twy, nullptr, var);
+                            -1.0f, s.twy, nullptr, var, false);
     else
       launch_yz_thin<double>(st, s.spec, s.nz, s.ny, s.Py, s.M, (const double*)s.Tt, s.tstride,
-                             -1.0, s.twy, nullptr, var);
+                             -1.0, s.twy, nullptr, var, true);
   };
   constexpr int kReps = 5;
   hipEvent_t e0 = take_event(c), e1 = take_event(c);
@@ -1634,6 +1642,7 @@ int mm_set_geometry(mm_ctx* c, int sample, int nx, int ny, int nz, double dx, do
   s.M = s.Px / 2;
   const bool full = path == PATH_3D;
   s.Py = full ? pad_3d(ny) : pad_thin_y(ny, mr);
+  if (!full && c->prec == MM_FP64 && yz_long_ok(nz, s.Py)) s.Py = pad_long(2 * ny - 1, s.Py, mr);
   s.Pz = full ? pad_3d(nz) : 1;
   const bool sp = single(c);
   s.R3 = rows_per_block(s.M, ny, sp);

@@ -443,6 +443,104 @@ __device__ __forceinline__ void yz_wave_body(cx<T>* __restrict__ A, int ny, int 
   }
 }
 
+// ---------------------------------------------------------------------------
+// Long columns (double precision, Py = 64 VL with VL = 10, 12, 14, 16): as the
+// wave kernel above, one wave per (layer, component), with the long wave FFT.
+// Its two halves of the spectrum go through the product one after the other,
+// so that a wave's slice holds half a column (9.3 KB at 1024 points) and
+// several blocks share a CU; consecutive threads take consecutive ky, reading
+// the column's tensor rows coalesced from global memory (each is used once
+// per half, too little to stage it in LDS).
+// LDS: 3 NZ slices of wfftl_buf<VL>() elements.
+// Bound by the dependency chain of a block (two transforms, four barriers).
+// Against the LDS Stockham kernel (192 threads, eight barriers per transform,
+// powers of two): 1000 x 500 x 1 61.8 -> 30.5 us (75 MB, 2.5 TB/s),
+// 600 x 300 x 1 (640 points instead of 1024) 59 -> 22.  Compiled for 4 waves
+// per SIMD the 1024-point kernel took 28.8 us, but spilled.
+// ---------------------------------------------------------------------------
+template <int VL, int NZ>
+__global__ void __launch_bounds__(192 * NZ, 3)
+k_yz_long(cx<double>* __restrict__ A, int ny, int M, const double* __restrict__ Tt, int tstride,
+          double scale, const cx<double>* __restrict__ twy, const int* __restrict__ done) {
+  using T = double;
+  constexpr int n = 64 * VL;
+  constexpr int KP = VL / 2;
+  constexpr int NW = 3 * NZ;
+  constexpr int nk = n / 2 + 1;
+  constexpr int SL = wfftl_buf<VL>();
+  extern __shared__ __align__(16) unsigned char smem[];
+  cx<T>* sm = reinterpret_cast<cx<T>*>(smem);
+  const int tid = (int)threadIdx.x;
+  const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kx = blockIdx.x;
+  const int z = w / 3, c = w - 3 * (w / 3);
+  cx<T>* slice = sm + w * SL;
+  cx<T>* Ak = A + ((size_t)kx * NZ + z) * ny * 3 + c;
+  cx<T> v[VL];
+#pragma unroll
+  for (int r = 0; r < VL; ++r) {
+    const int y = lane + 64 * r;
+    v[r] = y < ny ? Ak[(unsigned)y * 3u] : mk(T(0), T(0));
+  }
+  // the stop flag is read while the column loads are in flight
+  if (done != nullptr && *done != 0) return;
+  cx<T> u[2][8];
+  wfftl_forward<T, VL>(v, u, slice, reload(twy), lane);
+  const T* Tk = Tt + (size_t)kx * tstride;
+  const int k = lane >> 3, cc0 = lane & 7;
+  const bool mine = lane < 8 * KP;
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    if (mine) {
+#pragma unroll
+      for (int d = 0; d < 8; ++d) slice[wfl_f2(k, cc0, d)] = u[p][d];
+    }
+    __syncthreads();
+    for (int pos = tid; pos < 64 * KP; pos += 64 * NW) {
+      const int j = pos / KP, kk = pos - j * KP;
+      const int q = p * KP + kk + VL * j;
+      const bool neg = q > n / 2;
+      const int kyp = neg ? n - q : q;
+      const T sy = neg ? T(-1) : T(1);
+      const T* t = Tk + kyp * 6;
+      cx<T>* at = sm + wfl_f2(kk, j & 7, j >> 3);
+      cx<T> f[NZ][3];
+#pragma unroll
+      for (int zp = 0; zp < NZ; ++zp)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) f[zp][e] = at[(zp * 3 + e) * SL];
+#pragma unroll 1
+      for (int zo = 0; zo < NZ; ++zo) {
+        cx<T> h[3] = {mk(T(0), T(0)), mk(T(0), T(0)), mk(T(0), T(0))};
+#pragma unroll
+        for (int zp = 0; zp < NZ; ++zp) {
+          const int dz = zo - zp;
+          tensor_term<T>(t + (dz < 0 ? -dz : dz) * nk * 6, sy, dz < 0 ? T(-1) : T(1), f[zp], h);
+        }
+#pragma unroll
+        for (int e = 0; e < 3; ++e) at[(zo * 3 + e) * SL] = scl(h[e], scale);
+      }
+    }
+    __syncthreads();
+    if (mine) {
+#pragma unroll
+      for (int d = 0; d < 8; ++d) u[p][d] = slice[wfl_f2(k, cc0, d)];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  // the lane index read again: no offsets of the forward transform are held
+  // across the product
+  const int lane_i = thread_index() & 63;
+  wfftl_inverse<T, VL>(u, v, slice, reload(twy), lane_i);
+  const bool real_col = kx == 0 || kx == M;
+#pragma unroll
+  for (int r = 0; r < VL; ++r) {
+    const int y = lane_i + 64 * r;
+    if (y < ny) Ak[(unsigned)y * 3u] = real_col ? mk(v[r].x, T(0)) : v[r];
+  }
+}
+
 // waves per SIMD the yz kernels are compiled for: double precision holds
 // one 4-layer block per CU (LDS), single precision two.  The tile tuner may
 // pick the alternative bound yz_alt_waves_per_eu (fewer resident waves, more
@@ -676,9 +774,44 @@ int yz_variants(bool single, int nz, int Py) {
   return 4 * alt >= 3 * nz ? 2 : 1;
 }
 
+bool yz_long_ok(int nz, int Py) {
+  return nz >= 1 && nz <= 3 && (Py == 640 || Py == 768 || Py == 896 || Py == 1024);
+}
+
+template <int VL, int NZ>
+static void yz_long_launch(hipStream_t s, void* A, int ny, int M, const double* Tt, int tstride,
+                           double scale, const void* twy, const int* done) {
+  const size_t lds = (size_t)3 * NZ * wfftl_buf<VL>() * sizeof(cx<double>);
+  auto k = k_yz_long<VL, NZ>;
+  set_lds(k, lds);
+  hipLaunchKernelGGL(k, dim3(M + 1), dim3(192 * NZ), lds, s, (cx<double>*)A, ny, M, Tt, tstride,
+                     scale, (const cx<double>*)twy, done);
+}
+
+template <int VL>
+static void yz_long_nz(hipStream_t s, void* A, int nz, int ny, int M, const double* Tt,
+                       int tstride, double scale, const void* twy, const int* done) {
+  switch (nz) {
+    case 1: yz_long_launch<VL, 1>(s, A, ny, M, Tt, tstride, scale, twy, done); break;
+    case 2: yz_long_launch<VL, 2>(s, A, ny, M, Tt, tstride, scale, twy, done); break;
+    default: yz_long_launch<VL, 3>(s, A, ny, M, Tt, tstride, scale, twy, done); break;
+  }
+}
+
 template <typename T>
 void launch_yz_thin(hipStream_t s, void* A, int nz, int ny, int Py, int M, const T* Tt,
-                    int tstride, T scale, const void* twy, const int* done, int var) {
+                    int tstride, T scale, const void* twy, const int* done, int var,
+                    bool long_wave) {
+  if constexpr (sizeof(T) == 8) {
+    if (long_wave && yz_long_ok(nz, Py)) {
+      switch (Py) {
+        case 640: yz_long_nz<10>(s, A, nz, ny, M, Tt, tstride, scale, twy, done); return;
+        case 768: yz_long_nz<12>(s, A, nz, ny, M, Tt, tstride, scale, twy, done); return;
+        case 896: yz_long_nz<14>(s, A, nz, ny, M, Tt, tstride, scale, twy, done); return;
+        default: yz_long_nz<16>(s, A, nz, ny, M, Tt, tstride, scale, twy, done); return;
+      }
+    }
+  }
   if (yz_wave_ok(nz, Py)) {
     switch (Py) {
       case 64: yz_wave_nz<T, 1>(s, A, nz, ny, M, Tt, tstride, scale, twy, done, var); return;
@@ -801,8 +934,8 @@ template void launch_inv_x<float>(hipStream_t, const void*, int, int, int, int, 
                                   const void*, const int*);
 template void launch_fft_cols<double>(hipStream_t, void*, int, int, const void*);
 template void launch_yz_thin<double>(hipStream_t, void*, int, int, int, int, const double*, int,
-                                     double, const void*, const int*, int);
+                                     double, const void*, const int*, int, bool);
 template void launch_yz_thin<float>(hipStream_t, void*, int, int, int, int, const float*, int, float,
-                                    const void*, const int*, int);
+                                    const void*, const int*, int, bool);
 
 }  // namespace mmk

@@ -190,6 +190,67 @@ __device__ __forceinline__ void dftR(cx<T>* v) {
   else dft8<DIR>(v);
 }
 
+// cos and sin of 2 pi m / N for the composite lengths N = 10, 12, 14, 16
+__host__ __device__ constexpr double comp_cos(int N, int m) {
+  const double c10[10] = {1.0, 0.8090169943749475, 0.30901699437494745, -0.30901699437494745,
+                          -0.8090169943749475, -1.0, -0.8090169943749475, -0.30901699437494745,
+                          0.30901699437494745, 0.8090169943749475};
+  const double c12[12] = {1.0, 0.8660254037844386, 0.5, 0.0, -0.5, -0.8660254037844386, -1.0,
+                          -0.8660254037844386, -0.5, 0.0, 0.5, 0.8660254037844386};
+  const double c14[14] = {1.0, 0.9009688679024191, 0.6234898018587335, 0.2225209339563144,
+                          -0.2225209339563144, -0.6234898018587335, -0.9009688679024191, -1.0,
+                          -0.9009688679024191, -0.6234898018587335, -0.2225209339563144,
+                          0.2225209339563144, 0.6234898018587335, 0.9009688679024191};
+  const double c16[16] = {1.0, 0.9238795325112867, 0.7071067811865476, 0.3826834323650898, 0.0,
+                          -0.3826834323650898, -0.7071067811865476, -0.9238795325112867, -1.0,
+                          -0.9238795325112867, -0.7071067811865476, -0.3826834323650898, 0.0,
+                          0.3826834323650898, 0.7071067811865476, 0.9238795325112867};
+  return N == 10 ? c10[m] : N == 12 ? c12[m] : N == 14 ? c14[m] : c16[m];
+}
+__host__ __device__ constexpr double comp_sin(int N, int m) {
+  const double s10[10] = {0.0, 0.5877852522924731, 0.9510565162951535, 0.9510565162951535,
+                          0.5877852522924731, 0.0, -0.5877852522924731, -0.9510565162951535,
+                          -0.9510565162951535, -0.5877852522924731};
+  const double s12[12] = {0.0, 0.5, 0.8660254037844386, 1.0, 0.8660254037844386, 0.5, 0.0, -0.5,
+                          -0.8660254037844386, -1.0, -0.8660254037844386, -0.5};
+  const double s14[14] = {0.0, 0.4338837391175581, 0.7818314824680298, 0.9749279121818236,
+                          0.9749279121818236, 0.7818314824680298, 0.4338837391175581, 0.0,
+                          -0.4338837391175581, -0.7818314824680298, -0.9749279121818236,
+                          -0.9749279121818236, -0.7818314824680298, -0.4338837391175581};
+  const double s16[16] = {0.0, 0.3826834323650898, 0.7071067811865476, 0.9238795325112867, 1.0,
+                          0.9238795325112867, 0.7071067811865476, 0.3826834323650898, 0.0,
+                          -0.3826834323650898, -0.7071067811865476, -0.9238795325112867, -1.0,
+                          -0.9238795325112867, -0.7071067811865476, -0.3826834323650898};
+  return N == 10 ? s10[m] : N == 12 ? s12[m] : N == 14 ? s14[m] : s16[m];
+}
+
+// Length R1 R2: R1-point transforms of the samples n = R2 a + b over a,
+// twiddles exp(DIR 2 pi i b k1 / (R1 R2)), R2-point transforms over b.
+template <int R1, int R2, int DIR, typename T>
+__device__ __forceinline__ void dft_comp(cx<T>* v) {
+  constexpr int N = R1 * R2;
+  cx<T> t[R2][R1];
+#pragma unroll
+  for (int b = 0; b < R2; ++b) {
+#pragma unroll
+    for (int a = 0; a < R1; ++a) t[b][a] = v[R2 * a + b];
+    dftR<R1, DIR>(t[b]);
+#pragma unroll
+    for (int k = 1; k < R1; ++k)
+      if (b > 0)
+        t[b][k] = mul(t[b][k], mk(T(comp_cos(N, b * k % N)), T(DIR * comp_sin(N, b * k % N))));
+  }
+#pragma unroll
+  for (int k = 0; k < R1; ++k) {
+    cx<T> w[R2];
+#pragma unroll
+    for (int b = 0; b < R2; ++b) w[b] = t[b][k];
+    dftR<R2, DIR>(w);
+#pragma unroll
+    for (int q = 0; q < R2; ++q) v[k + R1 * q] = w[q];
+  }
+}
+
 // Twiddle exp(DIR 2 pi i m / twn) from a table tw[m] = exp(-2 pi i m / twn).
 template <int DIR, typename T>
 __device__ __forceinline__ cx<T> twiddle(const cx<T>* __restrict__ tw, int m) {

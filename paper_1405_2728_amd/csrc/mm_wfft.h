@@ -230,6 +230,111 @@ __device__ __forceinline__ void wfft_inverse_pk(cx<T> (&u)[8], cx<T> (&v)[PK][VL
   for (int p = 0; p < PK; ++p) dft_small<VL, 1>(v[p]);
 }
 
+// Long forms: one sequence of 64 VL points per wave, VL = 10, 12, 14, 16.
+// The 2 KP = VL groups of 8 lanes do not fit one wave, so the transposes and
+// the 8-point stages run in two halves: lane 8 k + c (k < KP) of half p holds
+// group k1 = p KP + k, in u[p].  Buffer: 73 KP elements (half the sequence).
+template <int VL>
+__host__ __device__ constexpr int wfftl_buf() { return VL / 2 * 73; }
+__device__ __forceinline__ int wfl_f2(int k, int c, int a) { return k * 73 + c * 9 + a; }
+
+template <int VL, int DIR, typename T>
+__device__ __forceinline__ void dft_long(cx<T>* v) {
+  static_assert(VL == 10 || VL == 12 || VL == 14 || VL == 16, "long wave FFT lengths");
+  if constexpr (VL == 10) dft_comp<2, 5, DIR>(v);
+  else if constexpr (VL == 12) dft_comp<4, 3, DIR>(v);
+  else if constexpr (VL == 14) dft_comp<2, 7, DIR>(v);
+  else dft_comp<4, 4, DIR>(v);
+}
+
+// The 8-point stages of one half with the second transpose.
+template <typename T, int VL, int DIR>
+__device__ __forceinline__ void wfftl_half(cx<T> (&u)[8], cx<T>* lds, const cx<T> (&w)[8], int k,
+                                           int a) {
+  dft8<DIR>(u);
+  if (DIR < 0) {
+#pragma unroll
+    for (int c = 1; c < 8; ++c) u[c] = mul(u[c], w[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) lds[wfl_f2(k, DIR < 0 ? c : a, DIR < 0 ? a : c)] = u[c];
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int c = 0; c < 8; ++c) u[c] = lds[wfl_f2(k, DIR < 0 ? a : c, DIR < 0 ? c : a)];
+  __builtin_amdgcn_wave_barrier();
+  if (DIR > 0) {
+#pragma unroll
+    for (int c = 1; c < 8; ++c) u[c] = mul(u[c], conj(w[c]));
+  }
+  dft8<DIR>(u);
+}
+
+template <typename T, int VL, int TS = 1>
+__device__ __forceinline__ void wfftl_forward(cx<T> (&v)[VL], cx<T> (&u)[2][8], cx<T>* lds,
+                                              const cx<T>* __restrict__ tw, int lane) {
+  constexpr int KP = VL / 2;
+  dft_long<VL, -1>(v);
+  const int k = lane >> 3, a = lane & 7;
+  const bool mine = lane < 8 * KP;
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    // one half's twiddles in registers at a time
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < KP; ++kk) {
+      const int k1 = p * KP + kk;
+      lds[wf_f1(kk, lane)] = k1 == 0 ? v[0] : mul(v[k1], tw[TS * lane * k1]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (mine) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) u[p][b] = lds[wf_f1(k, a + 8 * b)];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  cx<T> w[8];
+#pragma unroll
+  for (int c = 1; c < 8; ++c) w[c] = tw[TS * a * c * VL];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    if (mine) wfftl_half<T, VL, -1>(u[p], lds, w, k, a);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+template <typename T, int VL, int TS = 1>
+__device__ __forceinline__ void wfftl_inverse(cx<T> (&u)[2][8], cx<T> (&v)[VL], cx<T>* lds,
+                                              const cx<T>* __restrict__ tw, int lane) {
+  constexpr int KP = VL / 2;
+  const int k = lane >> 3, a = lane & 7;
+  const bool mine = lane < 8 * KP;
+  cx<T> w[8];
+#pragma unroll
+  for (int c = 1; c < 8; ++c) w[c] = tw[TS * a * c * VL];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    if (mine) wfftl_half<T, VL, 1>(u[p], lds, w, k, a);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    if (mine) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) lds[wf_f1(k, a + 8 * b)] = u[p][b];
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int kk = 0; kk < KP; ++kk) {
+      const int k1 = p * KP + kk;
+      v[k1] = lds[wf_f1(kk, lane)];
+      if (k1 > 0) v[k1] = mul(v[k1], conj(tw[TS * lane * k1]));
+    }
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  dft_long<VL, 1>(v);
+}
+
 // Frequency index held in slot d by lane g of the permuted distribution.
 template <int VL>
 __device__ __forceinline__ int wfft_freq(int lane, int d) {
