@@ -192,10 +192,11 @@ int pad_x(int nx, bool mr) { return nx < 2 ? 2 : pad_wave(2 * nx - 1, 128, mr); 
 int pad_thin_y(int ny, bool mr) { return pad_wave(2 * ny - 1, 64, mr); }
 // Lengths of the double-precision contexts beyond the wave FFT's 512 points:
 // the long wave FFT takes 64 VL points, VL = 10, 12, 14, 16, where the power
-// of two would be 1024 (the grids accepted are those of the powers of two).
-int pad_long(int n, int p, bool mr) {
-  if (p != 1024 || !mr) return p;
-  const int w = (n + 127) / 128 * 128;
+// of two would be 1024 (the grids accepted are those of the powers of two);
+// unit: 128 for columns, 256 for rows (half-length transforms).
+int pad_long(int n, int unit, int p, bool mr) {
+  if (p != 8 * unit || !mr) return p;
+  const int w = (n + unit - 1) / unit * unit;
   return w < p ? w : p;
 }
 int pad_3d(int n) {
@@ -614,12 +615,12 @@ void enqueue_reference(mm_ctx* c, Sample& s, const double* m, const MinState* ms
   const int* done = mst ? &mst->done : nullptr;
   Timer t(c, KID_REF);
   launch_xf<double>(st, const_cast<double*>(m), (const double*)nullptr, (double*)nullptr, mst,
-                    s.nx, s.ny, s.nz, s.Px, v.R, v.spec, v.twx, nullptr, s.mref);
+                    s.nx, s.ny, s.nz, s.Px, v.R, v.spec, v.twx, nullptr, s.mref, nullptr, false);
   enqueue_demag_mid(c, s, v, done, false);
   LocalArgs a = local_args(s);
   a.m = m;
   a.done = done;
-  launch_xil<double>(st, v.spec, a, s.Px, v.R, s.hdref, nullptr, v.twx);
+  launch_xil<double>(st, v.spec, a, s.Px, v.R, s.hdref, nullptr, v.twx, false);
   s.ref_age = 0;
 }
 
@@ -652,10 +653,10 @@ void enqueue_eval(mm_ctx* c, Sample& s, const double* m, const EvalOut& o) {
     Timer t(c, KID_XF);
     if (v.sp)
       launch_xf<float>(st, mm, as<float>(gx), as<float>(sx), mst, s.nx, s.ny, s.nz, s.Px, v.R,
-                       v.spec, v.twx, corr ? s.mref : nullptr, nullptr, &fz);
+                       v.spec, v.twx, corr ? s.mref : nullptr, nullptr, &fz, false);
     else
       launch_xf<double>(st, mm, as<double>(gx), as<double>(sx), mst, s.nx, s.ny, s.nz, s.Px, v.R,
-                        v.spec, v.twx, nullptr, nullptr, &fz);
+                        v.spec, v.twx, nullptr, nullptr, &fz, true);
   }
   enqueue_demag_mid(c, s, v, done, true);
   LocalArgs a = local_args(s, o.unit_A, o.zeeman);
@@ -674,9 +675,9 @@ void enqueue_eval(mm_ctx* c, Sample& s, const double* m, const EvalOut& o) {
   {
     Timer t(c, KID_XIL);
     if (v.sp)
-      launch_xil<float>(st, v.spec, a, s.Px, v.R, o.Hd, part, v.twx);
+      launch_xil<float>(st, v.spec, a, s.Px, v.R, o.Hd, part, v.twx, false);
     else
-      launch_xil<double>(st, v.spec, a, s.Px, v.R, o.Hd, part, v.twx);
+      launch_xil<double>(st, v.spec, a, s.Px, v.R, o.Hd, part, v.twx, true);
   }
   if (o.st_fin) {
     if (o.fuse_q >= 0) {
@@ -692,7 +693,7 @@ void enqueue_eval(mm_ctx* c, Sample& s, const double* m, const EvalOut& o) {
 // pass, sums reduced in one stage, no line search (whose trial logic reads
 // more of the state in the forward pass).
 bool fuse_ok(const mm_ctx* c, const Sample& s) {
-  return c->fused_finish && !c->ls.on && xf_fuses_finish(s.Px) &&
+  return c->fused_finish && !c->ls.on && xf_fuses_finish(s.Px, !single(c)) &&
          s.nb3 <= finish_single_stage_max();
 }
 
@@ -1183,12 +1184,12 @@ int time_rows(mm_ctx* c, Sample& s, int R, double* us) {
   auto pass = [&]() {
     if (sp) {
       launch_xf<float>(st, s.Hd, as<float>(s.g), as<float>(s.s), s.st_eval, s.nx, s.ny, s.nz,
-                       s.Px, R, s.spec, s.twx, nullptr, nullptr);
-      launch_xil<float>(st, s.spec, a, s.Px, R, nullptr, s.partials, s.twx);
+                       s.Px, R, s.spec, s.twx, nullptr, nullptr, nullptr, false);
+      launch_xil<float>(st, s.spec, a, s.Px, R, nullptr, s.partials, s.twx, false);
     } else {
       launch_xf<double>(st, s.Hd, as<double>(s.g), as<double>(s.s), s.st_eval, s.nx, s.ny,
-                        s.nz, s.Px, R, s.spec, s.twx, nullptr, nullptr);
-      launch_xil<double>(st, s.spec, a, s.Px, R, nullptr, s.partials, s.twx);
+                        s.nz, s.Px, R, s.spec, s.twx, nullptr, nullptr, nullptr, true);
+      launch_xil<double>(st, s.spec, a, s.Px, R, nullptr, s.partials, s.twx, true);
     }
   };
   constexpr int kReps = 5;
@@ -1639,10 +1640,11 @@ int mm_set_geometry(mm_ctx* c, int sample, int nx, int ny, int nz, double dx, do
   s.path = path;
   if (hipGetDevice(&s.dev) != hipSuccess) s.dev = -1;
   s.Px = pad_x(nx, mr);
+  if (c->prec == MM_FP64) s.Px = pad_long(2 * nx - 1, 256, s.Px, mr);
   s.M = s.Px / 2;
   const bool full = path == PATH_3D;
   s.Py = full ? pad_3d(ny) : pad_thin_y(ny, mr);
-  if (!full && c->prec == MM_FP64 && yz_long_ok(nz, s.Py)) s.Py = pad_long(2 * ny - 1, s.Py, mr);
+  if (!full && c->prec == MM_FP64 && yz_long_ok(nz, s.Py)) s.Py = pad_long(2 * ny - 1, 128, s.Py, mr);
   s.Pz = full ? pad_3d(nz) : 1;
   const bool sp = single(c);
   s.R3 = rows_per_block(s.M, ny, sp);

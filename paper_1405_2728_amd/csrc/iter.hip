@@ -217,10 +217,11 @@ __device__ __forceinline__ int wx_pad(int k) { return k + (k >> 3); }
 // order and arithmetic), then publishes the word the pass needs; every
 // other block's thread 0 polls for it.  Both return the word in every
 // thread of the block (block-uniform; they contain block barriers).
+template <int MAXT = kXwThreads>
 __device__ __forceinline__ double fin_decide(const FinFuse& fz) {
   __shared__ double s_w;
-  __shared__ double scratch[kNPartial * kXwThreads / 64];
-  finish_in_block<kXwThreads, 1>(fz.partials, fz.nb, fz.st, fz.Ms, fz.V, scratch);
+  __shared__ double scratch[kNPartial * MAXT / 64];
+  finish_in_block<MAXT, 1>(fz.partials, fz.nb, fz.st, fz.Ms, fz.V, scratch);
   if (threadIdx.x == 0) {
     const MinState* st = fz.st;   // this thread's own writes of the decision
     const double w = st->done != 0 ? kFinStop : (st->pending != 0 ? st->last_tau : kFinNoUpdate);
@@ -426,7 +427,7 @@ __device__ __forceinline__ void xf_w_body(double* __restrict__ m, const T* __res
       if (fz.partials != nullptr) {
         double w;
         if (blockIdx.x == 0) {
-          w = fin_decide(fz);
+          w = fin_decide<>(fz);
         } else {
           load(first);
           prefetched = true;
@@ -656,6 +657,254 @@ k_xil_w(const cx<T>* __restrict__ in, LocalArgs a, int R, double* __restrict__ H
   xil_w_body<T, VL>(in, a, R, Hd_out, partials, twx, xcd_remap(blockIdx.x, gridDim.x));
 }
 
+// ---------------------------------------------------------------------------
+// Long rows (double precision, M = 64 VL, VL = 10, 12, 14, 16): one row per
+// block, wave c transforms component c with the long wave FFT.  A region of
+// LDS per component holds in turn the row's samples, the transposes and the
+// spectrum, natural index k at xl_pad(k) = k + k / 16 (lanes VL apart on
+// different banks); three blocks share a CU at 1024 points.  The real-input
+// split runs where the spectrum is stored, straight from Z[k] and Z[M - k].
+// Bound by a block's chain of phases (loads, transform, stores or local
+// terms).  Against the LDS Stockham passes (powers of two; finish kernel):
+// xf + finish + xil of 1000 x 500 x 1 65.6 -> 50 us, of 600 x 300 x 1 (1280
+// points instead of 2048) 57 -> 40, of 700 x 450 x 2 112 -> 57.
+// ---------------------------------------------------------------------------
+constexpr int kXlThreads = 192;
+template <int VL>
+__host__ __device__ constexpr int xl_region() { return 68 * VL + 1; }
+__device__ __forceinline__ int xl_pad(int k) { return k + (k >> 4); }
+
+template <int VL, bool FUSE>
+__global__ void __launch_bounds__(kXlThreads, 3)
+k_xf_long(double* __restrict__ m, const double* __restrict__ g, double* __restrict__ sbuf,
+          const MinState* st, int nx, int ny, int nz, cx<double>* __restrict__ out,
+          const cx<double>* __restrict__ twx, FinFuse fz) {
+  using T = double;
+  constexpr int M = 64 * VL;
+  constexpr int KP = VL / 2;
+  constexpr int RG = xl_region<VL>();
+  // the state is read while the first cells' loads are in flight
+  int done = 0, pend = 0, ls = 0, retry = 0;
+  double tau = 0.0;
+  double* mbase = nullptr;
+  const T* g2 = nullptr;
+  if (st != nullptr) {
+    done = st->done;
+    pend = st->pending;
+    tau = st->last_tau;
+    ls = st->ls.on;
+    retry = st->ls_retry;
+    mbase = st->ls_mbase;
+    g2 = static_cast<const T*>(st->ls_g2);
+  }
+  extern __shared__ __align__(16) unsigned char smem[];
+  cx<T>* sm = reinterpret_cast<cx<T>*>(smem);
+  T* smr = reinterpret_cast<T*>(smem);
+  const int L = xcd_remap(blockIdx.x, gridDim.x);   // row z ny + y
+  const size_t N = (size_t)nx * ny * nz;
+  const size_t row0 = (size_t)L * nx;
+  const int tid = (int)threadIdx.x;
+  {
+    constexpr int U = 3;                       // cells in flight per thread
+    double mi[U][3], gi[U][3];
+    auto load = [&](int base) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int x = base + u * kXlThreads;
+        if (x < nx) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            mi[u][c] = m[c * N + row0 + x];
+            gi[u][c] = g != nullptr ? g[c * N + row0 + x] : 0.0;
+          }
+        }
+      }
+    };
+    bool prefetched = false;
+    if constexpr (FUSE) {
+      // as in the wave pass: block 0 decides, the others wait for its word
+      if (blockIdx.x == 0 && tid == 0) fz.st->fin_slot[fz.par ^ 1] = kFinSent;
+      if (fz.partials != nullptr) {
+        double w;
+        if (blockIdx.x == 0) {
+          w = fin_decide<kXlThreads>(fz);
+        } else {
+          load(tid);
+          prefetched = true;
+          w = fin_wait(fz);
+        }
+        const long long wb = __double_as_longlong(w);
+        const int lo = __builtin_amdgcn_readfirstlane((int)(wb & 0xffffffffll));
+        const int hi = __builtin_amdgcn_readfirstlane((int)(wb >> 32));
+        w = __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+        done = w == kFinStop ? 1 : 0;
+        pend = w > 0.0 ? 1 : 0;
+        tau = w;
+      }
+    }
+    const bool upd = pend != 0 && done == 0;
+    const bool ls_upd = upd && ls != 0;
+    for (int base = tid; base < nx; base += U * kXlThreads) {
+      if (!(prefetched && base == tid)) load(base);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int x = base + u * kXlThreads;
+        if (x >= nx) continue;
+        const size_t i = row0 + x;
+        if (ls_upd) {
+          // line search: see the wave pass
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            if (retry) {
+              mi[u][c] = mbase[c * N + i];
+            } else {
+              gi[u][c] = g2[c * N + i];
+              mbase[c * N + i] = mi[u][c];
+              const_cast<T*>(g)[c * N + i] = gi[u][c];
+            }
+          }
+        }
+        if (upd) {
+          double mo[3];
+          cayley_step(mi[u], gi[u], tau, mo);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            m[c * N + i] = mo[c];
+            sbuf[c * N + i] = mo[c] - mi[u][c];
+            mi[u][c] = mo[c];
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) smr[2 * (c * RG + (x >> 1)) + (x & 1)] = mi[u][c];
+      }
+    }
+  }
+  if (done != 0) return;
+  // zero padding x in [nx, 2M)
+  for (int c = 0; c < 3; ++c)
+    for (int x = nx + tid; x < 2 * M; x += kXlThreads) smr[2 * (c * RG + (x >> 1)) + (x & 1)] = T(0);
+  __syncthreads();
+  {
+    const int lane = tid & 63;
+    cx<T>* reg = sm + (size_t)(tid >> 6) * RG;
+    cx<T> v[VL], u[2][8];
+#pragma unroll
+    for (int q = 0; q < VL; ++q) v[q] = reg[lane + 64 * q];
+    __builtin_amdgcn_wave_barrier();
+    wfftl_forward<T, VL, 2>(v, u, reg, twx, lane);   // table of length Px = 2M
+    __builtin_amdgcn_wave_barrier();
+    if (lane < 8 * KP) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int d = 0; d < 8; ++d) reg[xl_pad(wfftl_freq<VL>(p, lane, d))] = u[p][d];
+    }
+  }
+  __syncthreads();
+  // X[k] = (Zk + Zc)/2 - i W^k (Zk - Zc)/2, 3 values per kx
+  const size_t slab = (size_t)3 * nz * ny;
+  cx<T>* dst = out + (size_t)L * 3;
+#pragma unroll 4
+  for (int idx = tid; idx < (M + 1) * 3; idx += kXlThreads) {
+    const int k = idx / 3, q = idx - k * 3;
+    const cx<T> zk = sm[q * RG + xl_pad(k < M ? k : 0)];
+    const cx<T> zc = conj(sm[q * RG + xl_pad(k == 0 ? 0 : M - k)]);
+    dst[k * slab + q] = scl(add(add(zk, zc), rot90<-1>(mul(twx[k], sub(zk, zc)))), T(0.5));
+  }
+}
+
+template <int VL>
+__global__ void __launch_bounds__(kXlThreads, 3)
+k_xil_long(const cx<double>* __restrict__ in, LocalArgs a, double* __restrict__ Hd_out,
+           double* __restrict__ partials, const cx<double>* __restrict__ twx) {
+  using T = double;
+  constexpr int M = 64 * VL;
+  constexpr int KP = VL / 2;
+  constexpr int RG = xl_region<VL>();
+  // state read while the spectrum loads are in flight
+  const int done = a.done != nullptr ? *a.done : 0;
+  const long long kst = a.st != nullptr ? a.st->k : 0;
+  const int lst = a.st != nullptr ? a.st->ls_trial : 0;
+  if (a.Hdyn != nullptr)
+    for (int c = 0; c < 3; ++c) a.H[c] = a.Hdyn[c];
+  extern __shared__ __align__(16) unsigned char smem[];
+  cx<T>* sm = reinterpret_cast<cx<T>*>(smem);
+  __shared__ double scratch[kNPartial * kXlThreads / 64];
+  const int nx = a.nx;
+  const size_t N = (size_t)nx * a.ny * a.nz;
+  const int L = xcd_remap(blockIdx.x, gridDim.x);
+  const int tid = (int)threadIdx.x;
+  const size_t slab = (size_t)3 * a.nz * a.ny;
+  const cx<T>* src = in + (size_t)L * 3;
+  {
+    constexpr int U = 8;                       // loads in flight per thread
+    constexpr int total = (M + 1) * 3;
+    for (int base = tid; base < total; base += U * kXlThreads) {
+      cx<T> e[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int idx = min(base + u * kXlThreads, total - 1);
+        const int k = idx / 3, q = idx - k * 3;
+        e[u] = src[k * slab + q];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int idx = base + u * kXlThreads;
+        const int k = idx / 3, q = idx - k * 3;
+        if (idx < total) sm[q * RG + xl_pad(k)] = e[u];
+      }
+    }
+  }
+  if (done != 0) return;
+  __syncthreads();
+  {
+    const int lane = tid & 63;
+    cx<T>* reg = sm + (size_t)(tid >> 6) * RG;
+    cx<T> v[VL], u[2][8];
+#pragma unroll
+    for (int q = 0; q < VL; ++q) {
+      const int k = lane + 64 * q;
+      const cx<T> Xk = reg[xl_pad(k)];
+      const cx<T> Xc = conj(reg[xl_pad(M - k)]);
+      const cx<T> wi = conj(twx[k]);
+      v[q] = conj(scl(add(add(Xk, Xc), rot90<1>(mul(wi, sub(Xk, Xc)))), T(0.5)));
+      if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_wave_barrier();
+    wfftl_forward<T, VL, 2>(v, u, reg, twx, lane);   // table of length Px = 2M
+    __builtin_amdgcn_wave_barrier();
+    if (lane < 8 * KP) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int d = 0; d < 8; ++d) reg[xl_pad(wfftl_freq<VL>(p, lane, d))] = conj(u[p][d]);
+    }
+  }
+  __syncthreads();
+  const bool bb = a.g != nullptr && a.s != nullptr && a.st != nullptr && (kst > 0 || lst != 0);
+  double part[kNPartial] = {};
+  for (int x = tid; x < nx; x += kXlThreads) {
+    const int i = L * nx + x;
+    CellIn cin;
+    fetch_cell<T>(a, i, bb, cin);
+    double hd[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const cx<T> e = sm[c * RG + xl_pad(x >> 1)];
+      hd[c] = (x & 1) ? e.y : e.x;
+    }
+    if (Hd_out != nullptr) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) Hd_out[c * N + i] = hd[c];
+    }
+    compute_cell<T>(a, i, hd, bb, cin, part);
+  }
+  bool is_max[kNPartial];
+  for (int q = 0; q < kNPartial; ++q) is_max[q] = q == kPartMax;
+  if (partials != nullptr)
+    block_reduce_store<kXlThreads>(part, is_max, scratch, partials + (size_t)L * kNPartial);
+}
+
 // ---- batched passes: one launch covers the blocks of several samples ---------
 // items[b] names the sample and its logical block; every sample of a launch
 // has the same transform length and rows per block.
@@ -830,18 +1079,52 @@ static void xil_wave(hipStream_t s, const void* in, const LocalArgs& a, int R, d
                      (const cx<T>*)twx);
 }
 
-// the wave-FFT forward pass (half lengths 64 VL, VL = 1..8) takes the finish over
-bool xf_fuses_finish(int Px) {
+// the wave-FFT forward passes (half lengths 64 VL, VL = 1..8; with long_wave
+// also VL = 10, 12, 14, 16) take the finish over
+bool xf_fuses_finish(int Px, bool long_wave) {
   const int M = Px / 2;
-  return Px % 2 == 0 && M % 64 == 0 && M >= 64 && M <= 512;
+  return Px % 2 == 0 && ((M % 64 == 0 && M >= 64 && M <= 512) || (long_wave && x_long_ok(M)));
+}
+
+bool x_long_ok(int M) { return M == 640 || M == 768 || M == 896 || M == 1024; }
+
+template <int VL>
+static void xf_long(hipStream_t s, double* m, const double* g, double* sbuf, const MinState* st,
+                    int nx, int ny, int nz, void* out, const void* twx, const FinFuse& fz) {
+  const size_t lds = (size_t)3 * xl_region<VL>() * sizeof(cx<double>);
+  auto k = fz.st != nullptr ? k_xf_long<VL, true> : k_xf_long<VL, false>;
+  set_lds(k, lds);
+  hipLaunchKernelGGL(k, dim3(nz * ny), dim3(kXlThreads), lds, s, m, g, sbuf, st, nx, ny, nz,
+                     (cx<double>*)out, (const cx<double>*)twx, fz);
+}
+
+template <int VL>
+static void xil_long(hipStream_t s, const void* in, const LocalArgs& a, double* Hd_out,
+                     double* partials, const void* twx) {
+  const size_t lds = (size_t)3 * xl_region<VL>() * sizeof(cx<double>);
+  auto k = k_xil_long<VL>;
+  set_lds(k, lds);
+  hipLaunchKernelGGL(k, dim3(a.nz * a.ny), dim3(kXlThreads), lds, s, (const cx<double>*)in, a,
+                     Hd_out, partials, (const cx<double>*)twx);
 }
 
 template <typename T>
 void launch_xf(hipStream_t s, double* m, const T* g, T* sbuf, const MinState* st, int nx, int ny,
                int nz, int Px, int R, void* out, const void* twx, const double* msub,
-               double* mcopy, const FinFuse* fzp) {
+               double* mcopy, const FinFuse* fzp, bool long_wave) {
   const FinFuse fz = fzp != nullptr ? *fzp : FinFuse{nullptr, nullptr, 0.0, 0.0, 0, 0, 0};
   const int M = Px / 2;
+  if constexpr (sizeof(T) == 8) {
+    // one row per block; no reference copy or difference (mixed form only)
+    if (long_wave && x_long_ok(M) && R == 1 && msub == nullptr && mcopy == nullptr) {
+      switch (M) {
+        case 640: xf_long<10>(s, m, g, sbuf, st, nx, ny, nz, out, twx, fz); return;
+        case 768: xf_long<12>(s, m, g, sbuf, st, nx, ny, nz, out, twx, fz); return;
+        case 896: xf_long<14>(s, m, g, sbuf, st, nx, ny, nz, out, twx, fz); return;
+        default: xf_long<16>(s, m, g, sbuf, st, nx, ny, nz, out, twx, fz); return;
+      }
+    }
+  }
   switch (M) {
     case 64: xf_wave<T, 1>(s, m, g, sbuf, st, nx, ny, nz, R, out, twx, msub, mcopy, fz); return;
     case 128: xf_wave<T, 2>(s, m, g, sbuf, st, nx, ny, nz, R, out, twx, msub, mcopy, fz); return;
@@ -871,8 +1154,18 @@ void launch_xf(hipStream_t s, double* m, const T* g, T* sbuf, const MinState* st
 
 template <typename T>
 void launch_xil(hipStream_t s, const void* in, const LocalArgs& a, int Px, int R, double* Hd_out,
-                double* partials, const void* twx) {
+                double* partials, const void* twx, bool long_wave) {
   const int M = Px / 2;
+  if constexpr (sizeof(T) == 8) {
+    if (long_wave && x_long_ok(M) && R == 1 && a.Hd_add == nullptr) {
+      switch (M) {
+        case 640: xil_long<10>(s, in, a, Hd_out, partials, twx); return;
+        case 768: xil_long<12>(s, in, a, Hd_out, partials, twx); return;
+        case 896: xil_long<14>(s, in, a, Hd_out, partials, twx); return;
+        default: xil_long<16>(s, in, a, Hd_out, partials, twx); return;
+      }
+    }
+  }
   switch (M) {
     case 64: xil_wave<T, 1>(s, in, a, R, Hd_out, partials, twx); return;
     case 128: xil_wave<T, 2>(s, in, a, R, Hd_out, partials, twx); return;
@@ -977,13 +1270,13 @@ template void launch_x_batched<float>(hipStream_t, bool, const BatchDesc*, const
                                       int, int);
 template void launch_xf<double>(hipStream_t, double*, const double*, double*, const MinState*, int,
                                 int, int, int, int, void*, const void*, const double*, double*,
-                                const FinFuse*);
+                                const FinFuse*, bool);
 template void launch_xf<float>(hipStream_t, double*, const float*, float*, const MinState*, int,
                                int, int, int, int, void*, const void*, const double*, double*,
-                               const FinFuse*);
+                               const FinFuse*, bool);
 template void launch_xil<double>(hipStream_t, const void*, const LocalArgs&, int, int, double*,
-                                 double*, const void*);
+                                 double*, const void*, bool);
 template void launch_xil<float>(hipStream_t, const void*, const LocalArgs&, int, int, double*,
-                                double*, const void*);
+                                double*, const void*, bool);
 
 }  // namespace mmk

@@ -307,18 +307,20 @@ int rows_per_block(int M, int ny, bool single);
 // msub (NULL: none) is subtracted from m before the transform; mcopy (NULL:
 // none) receives a copy of m, and then no pending update is applied.  fz
 // (NULL or fz->st NULL: none) hands the previous iteration's finish to the
-// pass; only the wave-FFT lengths take it (xf_fuses_finish).
+// pass; only the wave-FFT lengths take it (xf_fuses_finish).  long_wave: the
+// long wave kernels where x_long_ok (double-precision contexts, as above).
 template <typename T>
 void launch_xf(hipStream_t s, double* m, const T* g, T* sbuf, const MinState* st, int nx, int ny,
                int nz, int Px, int R, void* out, const void* twx, const double* msub,
-               double* mcopy, const FinFuse* fz = nullptr);
-bool xf_fuses_finish(int Px);
+               double* mcopy, const FinFuse* fz, bool long_wave);
+bool xf_fuses_finish(int Px, bool long_wave);
+bool x_long_ok(int M);
 // largest per-block sum count the finish kernel reduces in one stage
 int finish_single_stage_max();
 template <typename T>
 // partials: per-block sums out (NULL: none), reduced by launch_finish
 void launch_xil(hipStream_t s, const void* in, const LocalArgs& a, int Px, int R, double* Hd_out,
-                double* partials, const void* twx);
+                double* partials, const void* twx, bool long_wave);
 void launch_mean(hipStream_t s, const double* m, int N, double* partials, double* out3);
 
 // ---- derivatives (adjoint.hip) ------------------------------------------------

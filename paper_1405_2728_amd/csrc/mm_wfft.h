@@ -335,6 +335,12 @@ __device__ __forceinline__ void wfftl_inverse(cx<T> (&u)[2][8], cx<T> (&v)[VL], 
   dft_long<VL, 1>(v);
 }
 
+// Frequency held in slot d of half p by lane g (g < 8 KP).
+template <int VL>
+__device__ __forceinline__ int wfftl_freq(int p, int lane, int d) {
+  return p * (VL / 2) + (lane >> 3) + VL * ((lane & 7) + 8 * d);
+}
+
 // Frequency index held in slot d by lane g of the permuted distribution.
 template <int VL>
 __device__ __forceinline__ int wfft_freq(int lane, int d) {
