@@ -43,6 +43,7 @@ struct Sample {
   double dx = 0, dy = 0, dz = 0, V = 0;
   int path = PATH_NONE;
   int Px = 0, Py = 0, Pz = 1, M = 0, R3 = 1, nb3 = 0, tstride = 0;
+  bool small = false;         // fits one workgroup (small.hip)
   int yz_var = 0;             // occupancy variant of the thin yz wave kernel (tile tuner)
   double Ms = 0, A = 0, Ku = 0, u[3] = {1, 0, 0}, H[3] = {0, 0, 0};
   double* ku_map = nullptr;
@@ -624,6 +625,28 @@ void enqueue_reference(mm_ctx* c, Sample& s, const double* m, const MinState* ms
   s.ref_age = 0;
 }
 
+// Whether the sample runs in one workgroup (small.hip): double precision, a
+// thin film outside the wave FFT lengths (which batched sweeps share), no
+// line search; not while kernels are timed, which is per pass.
+bool small_ok(const mm_ctx* c, const Sample& s) {
+  return s.small && !c->ls.on && c->prof == 0;
+}
+
+// nit iterations on m (nit > 0), or one evaluation
+void enqueue_small(mm_ctx* c, Sample& s, const double* m, const EvalOut& o, int nit) {
+  LocalArgs a = local_args(s, o.unit_A, o.zeeman);
+  a.m = m;
+  a.g = nit > 0 ? s.g : nullptr;
+  a.Hout = o.H;
+  a.Hex_out = o.Hex;
+  a.Han_out = o.Han;
+  a.done = nit > 0 ? &s.st->done : o.done;
+  const double scale = -s.Ms / ((double)s.M * (double)s.Py);
+  launch_small(c->stream, a, const_cast<double*>(m), as<double>(s.s), nit,
+               nit > 0 ? s.st : o.st_fin, s.M, s.Py, (const double*)s.Tt, s.tstride, scale, s.twx,
+               s.twy, o.Hd, s.Ms, s.V);
+}
+
 // m is updated in place when o.iterate and an update is pending.  A
 // minimiser iteration of a single-precision context with a reference
 // transforms m - mref and adds hdref.  o.fuse_q >= 0 (an iteration at that
@@ -631,6 +654,10 @@ void enqueue_reference(mm_ctx* c, Sample& s, const double* m, const MinState* ms
 // the previous iteration's finish over and this iteration's is left pending.
 void enqueue_eval(mm_ctx* c, Sample& s, const double* m, const EvalOut& o) {
   if (o.fuse_q <= 0) flush_finish(c, s);
+  if (small_ok(c, s)) {
+    enqueue_small(c, s, m, o, o.iterate ? 1 : 0);
+    return;
+  }
   hipStream_t st = c->stream;
   FinFuse fz{nullptr, nullptr, s.Ms, s.V, s.nb3, 0, c->fin_spin};
   if (o.fuse_q >= 0) {
@@ -708,6 +735,17 @@ void enqueue_iteration(mm_ctx* c, Sample& s, double* m, int q = -1) {
   o.fuse_q = q >= 0 && fuse_ok(c, s) ? q : -1;
   enqueue_eval(c, s, m, o);
   ++s.ref_age;
+}
+
+// n iterations of a batch that ends with its finish taken.
+void enqueue_iterations(mm_ctx* c, Sample& s, double* m, long long n) {
+  if (small_ok(c, s)) {
+    flush_finish(c, s);
+    enqueue_small(c, s, m, EvalOut(), (int)n);
+    return;
+  }
+  for (long long q = 0; q < n; ++q) enqueue_iteration(c, s, m, (int)q);
+  flush_finish(c, s);
 }
 
 double tau0_of(const mm_ctx* c, const Sample& s) { return c->tau0 > 0 ? c->tau0 : 1e-3 / s.Ms; }
@@ -1416,7 +1454,7 @@ int run_loop(mm_ctx* c, Sample& s, double* m, long long left, long long k0, long
              mm_min_result* out) {
   // full batches after the first replay a captured graph (use_graph on a
   // non-null stream, kernels not being timed); the first batch runs eagerly
-  const bool graph = c->use_graph && c->stream != nullptr && c->prof == 0;
+  const bool graph = c->use_graph && c->stream != nullptr && c->prof == 0 && !small_ok(c, s);
   // A captured batch starts with the reference pass of the defect
   // correction; with a reference younger than poll_every (a continued run)
   // the first batch ends where it falls due, so that the references come at
@@ -1436,8 +1474,7 @@ int run_loop(mm_ctx* c, Sample& s, double* m, long long left, long long k0, long
       HIPCHK(c, hipGraphLaunch(s.it_graph, c->stream));
       s.ref_age = c->poll_every;   // as after an eager batch
     } else {
-      for (long long q = 0; q < batch; ++q) enqueue_iteration(c, s, m, (int)q);
-      flush_finish(c, s);
+      enqueue_iterations(c, s, m, batch);
     }
     left -= batch;
     HIPCHK(c, hipGetLastError());
@@ -1647,6 +1684,13 @@ int mm_set_geometry(mm_ctx* c, int sample, int nx, int ny, int nz, double dx, do
   if (!full && c->prec == MM_FP64 && yz_long_ok(nz, s.Py)) s.Py = pad_long(2 * ny - 1, 128, s.Py, mr);
   s.Pz = full ? pad_3d(nz) : 1;
   const bool sp = single(c);
+  int small_m = 0, small_p = 0;
+  s.small = !full && !sp && (s.M < 64 || s.Py < 64) && small_shape(nx, ny, nz, small_m, small_p);
+  if (s.small) {
+    s.M = small_m;
+    s.Px = 2 * small_m;
+    s.Py = small_p;
+  }
   s.R3 = rows_per_block(s.M, ny, sp);
   s.nb3 = nz * ((ny + s.R3 - 1) / s.R3);
   const size_t creal = sp ? sizeof(float) : sizeof(double);
@@ -2219,8 +2263,7 @@ int mm_hysteresis_sweep(mm_ctx* c, double* const* m, const double* H, int n_fiel
     }
     for (int k = 0; k < S; ++k) {
       if (!running[k] || in_batch[k]) continue;
-      for (int q = 0; q < c->poll_every; ++q) enqueue_iteration(c, c->smp[k], m[k], q);
-      flush_finish(c, c->smp[k]);
+      enqueue_iterations(c, c->smp[k], m[k], c->poll_every);
     }
     ++polls;
     eager = false;

@@ -321,6 +321,15 @@ template <typename T>
 // partials: per-block sums out (NULL: none), reduced by launch_finish
 void launch_xil(hipStream_t s, const void* in, const LocalArgs& a, int Px, int R, double* Hd_out,
                 double* partials, const void* twx, bool long_wave);
+// ---- small thin films in one workgroup (small.hip) ----------------------------
+// nit > 0: a batch of at most nit minimiser iterations on mio = a.m, g = a.g
+// and s = sio with state st; nit == 0: one evaluation (outputs of a, Hd_out;
+// sums decided into st where set).  small_shape: the padded half length M of
+// the rows and length P of the columns where one workgroup holds the grid
+bool small_shape(int nx, int ny, int nz, int& M, int& P);
+void launch_small(hipStream_t s, const LocalArgs& a, double* mio, double* sio, int nit,
+                  MinState* st, int M, int P, const double* Tt, int tstride, double scale,
+                  const void* twx, const void* twy, double* Hd_out, double Ms, double V);
 void launch_mean(hipStream_t s, const double* m, int N, double* partials, double* out3);
 
 // ---- derivatives (adjoint.hip) ------------------------------------------------
