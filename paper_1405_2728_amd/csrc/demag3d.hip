@@ -213,19 +213,22 @@ __device__ __forceinline__ void z3_body(cx<T>* __restrict__ B, int nz, int Py,
   }
 }
 
-// Pencils per wave of the packed z pass (double precision, 64 and 128
-// points).  The 8-point stages of a 64 VL-point transform use 8 VL lanes, so
-// one short pencil per wave leaves most lanes idle in most of the work; PK
-// packed pencils keep 8 PK VL lanes busy at the registers of a 64 PK VL-point
-// transform.  One pencil -> packed: 100 x 75 x 20 (64 points) 111 -> 39 us,
-// 37 x 29 x 11 25 -> 12, 200 x 200 x 40 (128 points) 519 -> 334, 64^3 39 -> 30.
-// At 128 points 4 pencils (256 VGPRs, 2 waves per SIMD instead of 3) took 36
-// where 2 take 30 (48^3), and at 256 points 2 pencils 241 us where 1 takes 205
-// (128^3), so longer pencils stay unpacked.
-__host__ __device__ constexpr int z3_pack(int Pz) { return Pz == 64 ? 8 : Pz == 128 ? 2 : 1; }
+// Pencils per wave of the packed z pass (double-precision contexts).  The
+// 8-point stages of a 64 VL-point transform use 8 VL lanes, so one pencil of
+// less than 512 points per wave leaves lanes idle in most of the work; 8 / VL
+// packed pencils keep all 64 busy.  The pass is bound by its instructions
+// (split into groups of kx planes whose B stays in the memory-side cache, it
+// took the same time), so the three components also take each stage together
+// and share the twiddle loads (70 instead of 96 vector memory instructions a
+// wave at 256 points) and their address arithmetic.
+// One pencil, component by component -> packed, component by component ->
+// packed, together: 100 x 75 x 20 (64 points) 111 -> 35 -> 36 us, 64^3 (128)
+// 39 -> 29 -> 30, 200 x 200 x 40 (128) 516 -> 335 -> 253, 128^3 (256) 206 ->
+// 241 -> 160, 48 x 48 x 140 (512, one pencil) 107 -> - -> 73.
+__host__ __device__ constexpr int z3_pack(int Pz) { return Pz >= 512 ? 1 : 512 / Pz; }
 
 // Logical block L of the packed z pass: wave w takes PK consecutive pencils
-// (kx, ky .. ky + PK - 1); otherwise z3_body.
+// (kx, ky .. ky + PK - 1).
 template <int VL>
 __device__ __forceinline__ void z3_pk_body(cx<double>* __restrict__ B, int nz, int Py,
                                            const double* __restrict__ T3, int rstride,
@@ -235,7 +238,6 @@ __device__ __forceinline__ void z3_pk_body(cx<double>* __restrict__ B, int nz, i
   if (done != nullptr && *done != 0) return;
   constexpr int n = 64 * VL;
   constexpr int PK = z3_pack(n);
-  constexpr int NB = PK * VL == 8 ? 1 : 2;         // input buffers: the next component's loads ahead
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = thread_index();
   const int lane = tid & 63;
@@ -244,24 +246,18 @@ __device__ __forceinline__ void z3_pk_body(cx<double>* __restrict__ B, int nz, i
   cx<T>* tbuf = reinterpret_cast<cx<T>*>(smem) + w * (PK * VL * 72);
   cx<T>* P = B + (size_t)pen * nz * 3;
   cx<T> F[3][8];
-  cx<T> xin[NB][PK][VL];
-  auto load = [&](int c, cx<T> (&x)[PK][VL]) {
+  cx<T> x[3][PK][VL];
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
 #pragma unroll
     for (int p = 0; p < PK; ++p)
 #pragma unroll
       for (int r = 0; r < VL; ++r) {
         const int z = lane + 64 * r;
-        x[p][r] = z < nz ? (P + (size_t)p * nz * 3 + c)[(unsigned)z * 3u] : mk(T(0), T(0));
+        x[c][p][r] = z < nz ? (P + (size_t)p * nz * 3 + c)[(unsigned)z * 3u] : mk(T(0), T(0));
       }
-  };
-  load(0, xin[0]);
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (NB == 2 && c < 2) load(c + 1, xin[(c + 1) % NB]);
-    wfft_forward_pk<T, VL, PK>(xin[c % NB], F[c], tbuf, reload(twz), lane);
-    __builtin_amdgcn_sched_barrier(0);
-    if (NB == 1 && c < 2) load(c + 1, xin[0]);
-  }
+  wfft3_forward_pk<T, VL, PK>(x, F, tbuf, reload(twz), lane);
+  __builtin_amdgcn_sched_barrier(0);
   const int hy = Py >> 1;
   const int k = lane >> 3;
   const int kx = pen / Py;
@@ -292,23 +288,23 @@ __device__ __forceinline__ void z3_pk_body(cx<double>* __restrict__ B, int nz, i
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  wfft3_inverse_pk<T, VL, PK>(F, x, tbuf, reload(twz), lane);
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    cx<T> xo[PK][VL];
-    wfft_inverse_pk<T, VL, PK>(F[c], xo, tbuf, reload(twz), lane);
+  for (int p = 0; p < PK; ++p)
 #pragma unroll
-    for (int p = 0; p < PK; ++p)
+    for (int r = 0; r < VL; ++r) {
+      const int z = lane + 64 * r;
+      if (z < nz) {
 #pragma unroll
-      for (int r = 0; r < VL; ++r) {
-        const int z = lane + 64 * r;
-        if (z < nz) (P + (size_t)p * nz * 3 + c)[(unsigned)z * 3u] = xo[p][r];
+        for (int c = 0; c < 3; ++c) (P + (size_t)p * nz * 3 + c)[(unsigned)z * 3u] = x[c][p][r];
       }
-    __builtin_amdgcn_sched_barrier(0);
-  }
+    }
 }
 
+// up to 256 points compiled for 3 resident waves per SIMD (158 VGPRs, no
+// spill; 170 and 2 waves otherwise: 128^3 175 us instead of 160)
 template <int VL>
-__global__ void __launch_bounds__(64 * kZ3Waves, 3)
+__global__ void __launch_bounds__(64 * kZ3Waves, VL <= 4 ? 3 : 2)
 k_z3_pk(cx<double>* __restrict__ B, int nz, int Py, const double* __restrict__ T3, int rstride,
         double scale, const cx<double>* __restrict__ twz, const int* __restrict__ done) {
   z3_pk_body<VL>(B, nz, Py, T3, rstride, scale, twz, done, xcd_remap(blockIdx.x, gridDim.x));
@@ -341,7 +337,7 @@ __device__ __forceinline__ void w3_item(int stage, const BatchDesc& d, int L) {
   else if (stage > 0)
     y3_inv_body<T, VL, HALF>((cx<T>*)d.spec, (const cx<T>*)d.B, d.nz, d.ny, nzb, d.M,
                              (const cx<T>*)d.twy, &d.st->done, L);
-  else if constexpr (PACK && z3_pack(64 * VL) > 1)
+  else if constexpr (PACK)
     z3_pk_body<VL>((cx<double>*)d.B, d.nz, d.Py, (const double*)d.Tt, d.tstride, d.scale,
                    (const cx<double>*)d.twz, &d.st->done, L);
   else
@@ -442,12 +438,12 @@ template <typename T>
 void launch_z3(hipStream_t s, void* B, int nz, int Py, int Pz, int M, const T* T3, int rstride,
                T scale, const void* twz, const int* done, bool pack) {
   if constexpr (sizeof(T) == 8) {
-    if (pack && Pz == 64) {
-      z3_pk_dispatch<1>(s, B, nz, Py, M, T3, rstride, scale, twz, done);
-      return;
-    }
-    if (pack && Pz == 128) {
-      z3_pk_dispatch<2>(s, B, nz, Py, M, T3, rstride, scale, twz, done);
+    if (pack) {
+      auto go = Pz == 64    ? z3_pk_dispatch<1>
+                : Pz == 128 ? z3_pk_dispatch<2>
+                : Pz == 256 ? z3_pk_dispatch<4>
+                            : z3_pk_dispatch<8>;
+      go(s, B, nz, Py, M, T3, rstride, scale, twz, done);
       return;
     }
   }

@@ -142,92 +142,129 @@ __device__ __forceinline__ void wfft_inverse(cx<T> (&u)[8], cx<T> (&v)[VL], cx<T
   dft_small<VL, 1>(v);
 }
 
-// Packed forms: PK sequences of length 64 VL per wave (PK VL <= 8), lane l
-// holding x_p[l + 64 r] in v[p][r].  Group k = p VL + k1 of 8 lanes takes the
-// place of k1 above, so that short lengths keep 8 PK VL lanes busy in the
-// 8-point stages instead of 8 VL; every sequence sees the same operations.
+// Packed forms of the three components together: PK sequences of length
+// 64 VL per wave and component (PK VL <= 8), lane l holding x_p[l + 64 r] of
+// component c in v[c][p][r].  Group k = p VL + k1 of 8 lanes takes the place
+// of k1 above, so that short lengths keep 8 PK VL lanes busy in the 8-point
+// stages instead of 8 VL.  The components take each stage in turn: a twiddle
+// factor is loaded once for the three, and their exchanges, one after the
+// other through one buffer (a wave's LDS instructions run in order), overlap.
 // Transpose buffer: 72 PK VL elements.
 template <typename T, int VL, int PK, int TS = 1>
-__device__ __forceinline__ void wfft_forward_pk(cx<T> (&v)[PK][VL], cx<T> (&u)[8], cx<T>* lds,
-                                                const cx<T>* __restrict__ tw, int lane) {
+__device__ __forceinline__ void wfft3_forward_pk(cx<T> (&v)[3][PK][VL], cx<T> (&u)[3][8],
+                                                 cx<T>* lds, const cx<T>* __restrict__ tw,
+                                                 int lane) {
   constexpr int NG = 8 * VL * PK;
   static_assert(NG <= 64, "more groups than lanes");
 #pragma unroll
-  for (int p = 0; p < PK; ++p) dft_small<VL, -1>(v[p]);
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int p = 0; p < PK; ++p) dft_small<VL, -1>(v[c][p]);
 #pragma unroll
   for (int k1 = 1; k1 < VL; ++k1) {
     const cx<T> w = tw[TS * lane * k1];
 #pragma unroll
-    for (int p = 0; p < PK; ++p) v[p][k1] = mul(v[p][k1], w);
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int p = 0; p < PK; ++p) v[c][p][k1] = mul(v[c][p][k1], w);
   }
   const int k = lane >> 3, a = lane & 7;
 #pragma unroll
-  for (int p = 0; p < PK; ++p)
+  for (int c = 0; c < 3; ++c) {
 #pragma unroll
-    for (int k1 = 0; k1 < VL; ++k1) lds[wf_f1(p * VL + k1, lane)] = v[p][k1];
-  __builtin_amdgcn_wave_barrier();
+    for (int p = 0; p < PK; ++p)
+#pragma unroll
+      for (int k1 = 0; k1 < VL; ++k1) lds[wf_f1(p * VL + k1, lane)] = v[c][p][k1];
+    __builtin_amdgcn_wave_barrier();
+    if (lane < NG) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) u[c][b] = lds[wf_f1(k, a + 8 * b)];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
   if (lane < NG) {
 #pragma unroll
-    for (int b = 0; b < 8; ++b) u[b] = lds[wf_f1(k, a + 8 * b)];
-    dft8<-1>(u);
+    for (int c = 0; c < 3; ++c) dft8<-1>(u[c]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 1; c < 8; ++c) u[c] = mul(u[c], tw[TS * a * c * VL]);
-  }
-  __builtin_amdgcn_wave_barrier();
-  if (lane < NG) {
+    for (int cc = 1; cc < 8; ++cc) {
+      const cx<T> w = tw[TS * a * cc * VL];
 #pragma unroll
-    for (int cc = 0; cc < 8; ++cc) lds[wf_f2(k, cc, a)] = u[cc];
-  }
-  __builtin_amdgcn_wave_barrier();
-  if (lane < NG) {
+      for (int c = 0; c < 3; ++c) u[c][cc] = mul(u[c][cc], w);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int aa = 0; aa < 8; ++aa) u[aa] = lds[wf_f2(k, a, aa)];
-    dft8<-1>(u);
+    for (int c = 0; c < 3; ++c) {
+#pragma unroll
+      for (int cc = 0; cc < 8; ++cc) lds[wf_f2(k, cc, a)] = u[c][cc];
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int aa = 0; aa < 8; ++aa) u[c][aa] = lds[wf_f2(k, a, aa)];
+      __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dft8<-1>(u[c]);
   }
-  __builtin_amdgcn_wave_barrier();
 }
 
 template <typename T, int VL, int PK, int TS = 1>
-__device__ __forceinline__ void wfft_inverse_pk(cx<T> (&u)[8], cx<T> (&v)[PK][VL], cx<T>* lds,
-                                                const cx<T>* __restrict__ tw, int lane) {
+__device__ __forceinline__ void wfft3_inverse_pk(cx<T> (&u)[3][8], cx<T> (&v)[3][PK][VL],
+                                                 cx<T>* lds, const cx<T>* __restrict__ tw,
+                                                 int lane) {
   constexpr int NG = 8 * VL * PK;
   static_assert(NG <= 64, "more groups than lanes");
   const int k = lane >> 3, a = lane & 7;
   if (lane < NG) {
-    dft8<1>(u);
 #pragma unroll
-    for (int aa = 0; aa < 8; ++aa) lds[wf_f2(k, a, aa)] = u[aa];
-  }
-  __builtin_amdgcn_wave_barrier();
-  if (lane < NG) {
+    for (int c = 0; c < 3; ++c) dft8<1>(u[c]);
 #pragma unroll
-    for (int cc = 0; cc < 8; ++cc) u[cc] = lds[wf_f2(k, cc, a)];
+    for (int c = 0; c < 3; ++c) {
 #pragma unroll
-    for (int cc = 1; cc < 8; ++cc) u[cc] = mul(u[cc], conj(tw[TS * a * cc * VL]));
-    dft8<1>(u);
-  }
-  __builtin_amdgcn_wave_barrier();
-  if (lane < NG) {
+      for (int aa = 0; aa < 8; ++aa) lds[wf_f2(k, a, aa)] = u[c][aa];
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int b = 0; b < 8; ++b) lds[wf_f1(k, a + 8 * b)] = u[b];
-  }
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int p = 0; p < PK; ++p)
-#pragma unroll
-    for (int kk = 0; kk < VL; ++kk) {
-      const cx<T>& e = lds[wf_f1(p * VL + kk, lane)];
-      v[p][kk] = mk(e.x, e.y);
+      for (int cc = 0; cc < 8; ++cc) u[c][cc] = lds[wf_f2(k, cc, a)];
+      __builtin_amdgcn_wave_barrier();
     }
-  __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int cc = 1; cc < 8; ++cc) {
+      const cx<T> w = conj(tw[TS * a * cc * VL]);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) u[c][cc] = mul(u[c][cc], w);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dft8<1>(u[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    if (lane < NG) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) lds[wf_f1(k, a + 8 * b)] = u[c][b];
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int p = 0; p < PK; ++p)
+#pragma unroll
+      for (int kk = 0; kk < VL; ++kk) {
+        const cx<T>& e = lds[wf_f1(p * VL + kk, lane)];
+        v[c][p][kk] = mk(e.x, e.y);
+      }
+    __builtin_amdgcn_wave_barrier();
+  }
 #pragma unroll
   for (int kk = 1; kk < VL; ++kk) {
     const cx<T> w = conj(tw[TS * lane * kk]);
 #pragma unroll
-    for (int p = 0; p < PK; ++p) v[p][kk] = mul(v[p][kk], w);
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int p = 0; p < PK; ++p) v[c][p][kk] = mul(v[c][p][kk], w);
   }
 #pragma unroll
-  for (int p = 0; p < PK; ++p) dft_small<VL, 1>(v[p]);
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int p = 0; p < PK; ++p) dft_small<VL, 1>(v[c][p]);
 }
 
 // Long forms: one sequence of 64 VL points per wave, VL = 10, 12, 14, 16.
