@@ -568,8 +568,8 @@ void enqueue_demag_mid(mm_ctx* c, const Sample& s, const Conv& v, const int* don
     const double scale = -s.Ms / ((double)s.M * (double)s.Py * (double)s.Pz);
     {
       Timer t(c, KID_Y3F);
-      if (v.sp) launch_y3<float>(st, v.spec, v.B, s.nz, s.ny, s.Py, s.M, -1, v.twy, done);
-      else launch_y3<double>(st, v.spec, v.B, s.nz, s.ny, s.Py, s.M, -1, v.twy, done);
+      if (v.sp) launch_y3<float>(st, v.spec, v.B, s.nz, s.ny, s.Py, s.M, -1, v.twy, done, false);
+      else launch_y3<double>(st, v.spec, v.B, s.nz, s.ny, s.Py, s.M, -1, v.twy, done, !single(c));
     }
     {
       Timer t(c, KID_Z3);
@@ -582,8 +582,8 @@ void enqueue_demag_mid(mm_ctx* c, const Sample& s, const Conv& v, const int* don
     }
     {
       Timer t(c, KID_Y3I);
-      if (v.sp) launch_y3<float>(st, v.spec, v.B, s.nz, s.ny, s.Py, s.M, 1, v.twy, done);
-      else launch_y3<double>(st, v.spec, v.B, s.nz, s.ny, s.Py, s.M, 1, v.twy, done);
+      if (v.sp) launch_y3<float>(st, v.spec, v.B, s.nz, s.ny, s.Py, s.M, 1, v.twy, done, false);
+      else launch_y3<double>(st, v.spec, v.B, s.nz, s.ny, s.Py, s.M, 1, v.twy, done, !single(c));
     }
   } else {
     Timer t(c, KID_YZ);
@@ -962,7 +962,8 @@ int build_batch(mm_ctx* c, double* const* m, BatchPlan& P, const std::vector<cha
     std::vector<WorkItem> v;
     for (int i = 0; i < (int)d.size(); ++i) {
       if (!d[i].B) continue;
-      const int nb = st == 1 ? z3_blocks(d[i].Py, d[i].Pz, d[i].M, !sp) : y3_blocks(d[i].nz, d[i].M);
+      const int nb = st == 1 ? z3_blocks(d[i].Py, d[i].Pz, d[i].M, !sp)
+                             : y3_blocks(d[i].nz, d[i].Py, d[i].M, !sp);
       for (int blk = 0; blk < nb; ++blk) v.push_back({i, blk});
       const int len = st == 1 ? d[i].Pz : d[i].Py;
       L.lds = std::max(L.lds, w3_block_lds(sp, st - 1, len, !sp));

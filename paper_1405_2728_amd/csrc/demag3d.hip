@@ -213,7 +213,8 @@ __device__ __forceinline__ void z3_body(cx<T>* __restrict__ B, int nz, int Py,
   }
 }
 
-// Pencils per wave of the packed z pass (double-precision contexts).  The
+// Pencils (planes in the y passes) per wave of the packed passes
+// (double-precision contexts).  The
 // 8-point stages of a 64 VL-point transform use 8 VL lanes, so one pencil of
 // less than 512 points per wave leaves lanes idle in most of the work; 8 / VL
 // packed pencils keep all 64 busy.  The pass is bound by its instructions
@@ -225,7 +226,12 @@ __device__ __forceinline__ void z3_body(cx<T>* __restrict__ B, int nz, int Py,
 // packed, together: 100 x 75 x 20 (64 points) 111 -> 35 -> 36 us, 64^3 (128)
 // 39 -> 29 -> 30, 200 x 200 x 40 (128) 516 -> 335 -> 253, 128^3 (256) 206 ->
 // 241 -> 160, 48 x 48 x 140 (512, one pencil) 107 -> - -> 73.
-__host__ __device__ constexpr int z3_pack(int Pz) { return Pz >= 512 ? 1 : 512 / Pz; }
+__host__ __device__ constexpr int pack3(int P) { return P >= 512 ? 1 : 512 / P; }
+// blocks of the y passes per kx
+__host__ __device__ constexpr int y3_zblocks(int nz, int Py, bool pack) {
+  const int per = kY3Waves * (pack ? pack3(Py) : 1);
+  return (nz + per - 1) / per;
+}
 
 // Logical block L of the packed z pass: wave w takes PK consecutive pencils
 // (kx, ky .. ky + PK - 1).
@@ -237,7 +243,7 @@ __device__ __forceinline__ void z3_pk_body(cx<double>* __restrict__ B, int nz, i
   using T = double;
   if (done != nullptr && *done != 0) return;
   constexpr int n = 64 * VL;
-  constexpr int PK = z3_pack(n);
+  constexpr int PK = pack3(n);
   extern __shared__ __align__(16) unsigned char smem[];
   const int tid = thread_index();
   const int lane = tid & 63;
@@ -310,6 +316,118 @@ k_z3_pk(cx<double>* __restrict__ B, int nz, int Py, const double* __restrict__ T
   z3_pk_body<VL>(B, nz, Py, T3, rstride, scale, twz, done, xcd_remap(blockIdx.x, gridDim.x));
 }
 
+// Packed y passes (double-precision contexts): wave w of logical block L takes
+// the 8 / VL planes (kx, z0 ..), the three components together, for the same
+// reasons as the z pass; a store or load of B then also covers 8 / VL layers
+// (48 bytes each) in a piece.  One plane, component by component -> packed,
+// forward and inverse: 128^3 (256 points) 98 and 94 -> 84 and 77 us (304 MB
+// each: 3.6 and 3.9 TB/s), 48 x 48 x 140 (128) 31 and 27 -> 28 and 22,
+// 200 x 200 x 40 (512, one plane) 114 and 118 -> 114 and 104.
+template <int VL>
+__device__ __forceinline__ void y3_fwd_pk_body(const cx<double>* __restrict__ A,
+                                               cx<double>* __restrict__ B, int nz, int ny,
+                                               int nzb, const cx<double>* __restrict__ twy,
+                                               const int* __restrict__ done, int L) {
+  using T = double;
+  if (done != nullptr && *done != 0) return;
+  constexpr int n = 64 * VL;
+  constexpr int PK = 8 / VL;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = thread_index();
+  const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kx = L / nzb;
+  const int z0 = ((L - kx * nzb) * kY3Waves + w) * PK;
+  if (z0 >= nz) return;                      // no block barrier below
+  cx<T>* tbuf = reinterpret_cast<cx<T>*>(smem) + w * (PK * VL * 72);
+  const cx<T>* Ap = A + ((size_t)kx * nz + z0) * ny * 3;
+  cx<T> F[3][8];
+  cx<T> x[3][PK][VL];
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int p = 0; p < PK; ++p)
+#pragma unroll
+      for (int r = 0; r < VL; ++r) {
+        const int y = lane + 64 * r;
+        x[c][p][r] = y < ny && z0 + p < nz ? (Ap + (size_t)p * ny * 3 + c)[(unsigned)y * 3u]
+                                           : mk(T(0), T(0));
+      }
+  wfft3_forward_pk<T, VL, PK>(x, F, tbuf, reload(twy), lane);
+  const int k = lane >> 3;
+  if (PK == 1 || z0 + k / VL < nz) {
+    cx<T>* Bk = B + ((size_t)kx * n * nz + z0) * 3;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+      const unsigned ky = k % VL + VL * ((lane & 7) + 8 * d);
+      cx<T>* p = Bk + (ky * (unsigned)nz + k / VL) * 3u;
+      p[0] = F[0][d];
+      p[1] = F[1][d];
+      p[2] = F[2][d];
+    }
+  }
+}
+
+template <int VL>
+__global__ void __launch_bounds__(64 * kY3Waves, VL <= 4 ? 3 : 2)
+k_y3_fwd_pk(const cx<double>* __restrict__ A, cx<double>* __restrict__ B, int nz, int ny, int nzb,
+            const cx<double>* __restrict__ twy, const int* __restrict__ done) {
+  y3_fwd_pk_body<VL>(A, B, nz, ny, nzb, twy, done, xcd_remap(blockIdx.x, gridDim.x));
+}
+
+template <int VL>
+__device__ __forceinline__ void y3_inv_pk_body(cx<double>* __restrict__ A,
+                                               const cx<double>* __restrict__ B, int nz, int ny,
+                                               int nzb, int M, const cx<double>* __restrict__ twy,
+                                               const int* __restrict__ done, int L) {
+  using T = double;
+  if (done != nullptr && *done != 0) return;
+  constexpr int n = 64 * VL;
+  constexpr int PK = 8 / VL;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int tid = thread_index();
+  const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kx = L / nzb;
+  const int z0 = ((L - kx * nzb) * kY3Waves + w) * PK;
+  if (z0 >= nz) return;
+  cx<T>* tbuf = reinterpret_cast<cx<T>*>(smem) + w * (PK * VL * 72);
+  cx<T> F[3][8];
+  cx<T> x[3][PK][VL];
+  const int k = lane >> 3;
+  const cx<T>* Bk = B + ((size_t)kx * n * nz + z0) * 3;
+  const bool in = PK == 1 || z0 + k / VL < nz;
+#pragma unroll
+  for (int d = 0; d < 8; ++d) {
+    const unsigned ky = k % VL + VL * ((lane & 7) + 8 * d);
+    const cx<T>* p = Bk + (ky * (unsigned)nz + k / VL) * 3u;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) F[c][d] = in ? p[c] : mk(T(0), T(0));
+  }
+  wfft3_inverse_pk<T, VL, PK>(F, x, tbuf, reload(twy), lane);
+  const bool real_col = (kx == 0 || kx == M);
+  cx<T>* Ap = A + ((size_t)kx * nz + z0) * ny * 3;
+#pragma unroll
+  for (int p = 0; p < PK; ++p)
+#pragma unroll
+    for (int r = 0; r < VL; ++r) {
+      const int y = lane + 64 * r;
+      if (y < ny && z0 + p < nz) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          (Ap + (size_t)p * ny * 3 + c)[(unsigned)y * 3u] =
+              real_col ? mk(x[c][p][r].x, T(0)) : x[c][p][r];
+      }
+    }
+}
+
+template <int VL>
+__global__ void __launch_bounds__(64 * kY3Waves, VL <= 4 ? 3 : 2)
+k_y3_inv_pk(cx<double>* __restrict__ A, const cx<double>* __restrict__ B, int nz, int ny, int nzb,
+            int M, const cx<double>* __restrict__ twy, const int* __restrict__ done) {
+  y3_inv_pk_body<VL>(A, B, nz, ny, nzb, M, twy, done, xcd_remap(blockIdx.x, gridDim.x));
+}
+
 // FP64 up to 256 points: compiled for 3 resident waves per SIMD (168
 // VGPRs, no spill; 170 and 2 waves otherwise)
 template <typename T, int VL, bool HALF>
@@ -330,16 +448,25 @@ static_assert(kY3Waves == kZ3Waves, "the 3-D stages share one block size");
 template <typename T, int VL, bool PACK>
 __device__ __forceinline__ void w3_item(int stage, const BatchDesc& d, int L) {
   constexpr bool HALF = k3dHalf;
-  const int nzb = (d.nz + kY3Waves - 1) / kY3Waves;
+  const int nzb = y3_zblocks(d.nz, 64 * VL, PACK);
+  if constexpr (PACK) {
+    if (stage < 0)
+      y3_fwd_pk_body<VL>((const cx<double>*)d.spec, (cx<double>*)d.B, d.nz, d.ny, nzb,
+                         (const cx<double>*)d.twy, &d.st->done, L);
+    else if (stage > 0)
+      y3_inv_pk_body<VL>((cx<double>*)d.spec, (const cx<double>*)d.B, d.nz, d.ny, nzb, d.M,
+                         (const cx<double>*)d.twy, &d.st->done, L);
+    else
+      z3_pk_body<VL>((cx<double>*)d.B, d.nz, d.Py, (const double*)d.Tt, d.tstride, d.scale,
+                     (const cx<double>*)d.twz, &d.st->done, L);
+    return;
+  }
   if (stage < 0)
     y3_fwd_body<T, VL, HALF>((const cx<T>*)d.spec, (cx<T>*)d.B, d.nz, d.ny, nzb,
                              (const cx<T>*)d.twy, &d.st->done, L);
   else if (stage > 0)
     y3_inv_body<T, VL, HALF>((cx<T>*)d.spec, (const cx<T>*)d.B, d.nz, d.ny, nzb, d.M,
                              (const cx<T>*)d.twy, &d.st->done, L);
-  else if constexpr (PACK)
-    z3_pk_body<VL>((cx<double>*)d.B, d.nz, d.Py, (const double*)d.Tt, d.tstride, d.scale,
-                   (const cx<double>*)d.twz, &d.st->done, L);
   else
     z3_body<T, VL, HALF>((cx<T>*)d.B, d.nz, d.Py, (const T*)d.Tt, d.tstride, (T)d.scale,
                          (const cx<T>*)d.twz, &d.st->done, L);
@@ -369,12 +496,17 @@ static void set_lds(K kernel, size_t bytes) {
                               (int)bytes);
 }
 
+// LDS of a packed block: 72 elements per group of 8 lanes and wave
+static size_t pack3_lds(int P) {
+  return (size_t)kZ3Waves * pack3(P) * (P / 64) * 72 * sizeof(cx<double>);
+}
+
 template <typename T, int VL>
 static void y3_dispatch(hipStream_t s, void* A, void* B, int nz, int ny, int M, int dir,
                         const void* twy, const int* done) {
   constexpr bool HALF = k3dHalf;
   const size_t lds = (size_t)kY3Waves * wfft_buf<VL, HALF>() * sizeof(cx<T>);
-  const int nzb = (nz + kY3Waves - 1) / kY3Waves;
+  const int nzb = y3_zblocks(nz, 64 * VL, false);
   const dim3 grid((unsigned)((M + 1) * nzb));
   if (dir < 0) {
     auto k = k_y3_fwd<T, VL, HALF>;
@@ -389,9 +521,38 @@ static void y3_dispatch(hipStream_t s, void* A, void* B, int nz, int ny, int M, 
   }
 }
 
+template <int VL>
+static void y3_pk_dispatch(hipStream_t s, void* A, void* B, int nz, int ny, int M, int dir,
+                           const void* twy, const int* done) {
+  const size_t lds = pack3_lds(64 * VL);
+  const int nzb = y3_zblocks(nz, 64 * VL, true);
+  const dim3 grid((unsigned)((M + 1) * nzb));
+  if (dir < 0) {
+    auto k = k_y3_fwd_pk<VL>;
+    set_lds(k, lds);
+    hipLaunchKernelGGL(k, grid, dim3(64 * kY3Waves), lds, s, (const cx<double>*)A, (cx<double>*)B,
+                       nz, ny, nzb, (const cx<double>*)twy, done);
+  } else {
+    auto k = k_y3_inv_pk<VL>;
+    set_lds(k, lds);
+    hipLaunchKernelGGL(k, grid, dim3(64 * kY3Waves), lds, s, (cx<double>*)A, (const cx<double>*)B,
+                       nz, ny, nzb, M, (const cx<double>*)twy, done);
+  }
+}
+
 template <typename T>
 void launch_y3(hipStream_t s, void* A, void* B, int nz, int ny, int Py, int M, int dir,
-               const void* twy, const int* done) {
+               const void* twy, const int* done, bool pack) {
+  if constexpr (sizeof(T) == 8) {
+    if (pack) {
+      auto go = Py == 64    ? y3_pk_dispatch<1>
+                : Py == 128 ? y3_pk_dispatch<2>
+                : Py == 256 ? y3_pk_dispatch<4>
+                            : y3_pk_dispatch<8>;
+      go(s, A, B, nz, ny, M, dir, twy, done);
+      return;
+    }
+  }
   switch (Py) {
     case 64: y3_dispatch<T, 1>(s, A, B, nz, ny, M, dir, twy, done); break;
     case 128: y3_dispatch<T, 2>(s, A, B, nz, ny, M, dir, twy, done); break;
@@ -401,12 +562,7 @@ void launch_y3(hipStream_t s, void* A, void* B, int nz, int ny, int Py, int M, i
 }
 
 int z3_blocks(int Py, int Pz, int M, bool pack) {
-  return (M + 1) * (Py / (kZ3Waves * (pack ? z3_pack(Pz) : 1)));
-}
-
-// LDS of a packed z block: 72 elements per group of 8 lanes and wave
-static size_t z3_pk_lds(int Pz) {
-  return (size_t)kZ3Waves * z3_pack(Pz) * (Pz / 64) * 72 * sizeof(cx<double>);
+  return (M + 1) * (Py / (kZ3Waves * (pack ? pack3(Pz) : 1)));
 }
 
 template <typename T, int VL>
@@ -425,7 +581,7 @@ static void z3_dispatch(hipStream_t s, void* B, int nz, int Py, int M, const T* 
 template <int VL>
 static void z3_pk_dispatch(hipStream_t s, void* B, int nz, int Py, int M, const double* T3,
                            int rstride, double scale, const void* twz, const int* done) {
-  const size_t lds = z3_pk_lds(64 * VL);
+  const size_t lds = pack3_lds(64 * VL);
   // Py is a multiple of kZ3Waves PK (32 at most), so every wave owns PK pencils
   const dim3 grid((unsigned)z3_blocks(Py, 64 * VL, M, true));
   auto k = k_z3_pk<VL>;
@@ -455,7 +611,7 @@ void launch_z3(hipStream_t s, void* B, int nz, int Py, int Pz, int M, const T* T
   }
 }
 
-int y3_blocks(int nz, int M) { return (M + 1) * ((nz + kY3Waves - 1) / kY3Waves); }
+int y3_blocks(int nz, int Py, int M, bool pack) { return (M + 1) * y3_zblocks(nz, Py, pack); }
 
 template <typename T, int VL>
 static size_t w3_lds() {
@@ -464,7 +620,7 @@ static size_t w3_lds() {
 }
 
 size_t w3_block_lds(bool single, int stage, int P, bool pack) {
-  if (stage == 0 && pack) return z3_pk_lds(P);
+  if (pack) return pack3_lds(P);
   switch (P) {
     case 64: return single ? w3_lds<float, 1>() : w3_lds<double, 1>();
     case 128: return single ? w3_lds<float, 2>() : w3_lds<double, 2>();
@@ -475,11 +631,14 @@ size_t w3_block_lds(bool single, int stage, int P, bool pack) {
 
 template <typename T>
 static const void* w3_kernel(int stage, bool pack) {
-  if (stage < 0) return (const void*)k_w3_p<T, -1, false>;
-  if (stage > 0) return (const void*)k_w3_p<T, 1, false>;
   if constexpr (sizeof(T) == 8)
-    if (pack) return (const void*)k_w3_p<T, 0, true>;
-  return (const void*)k_w3_p<T, 0, false>;
+    if (pack)
+      return stage < 0   ? (const void*)k_w3_p<T, -1, true>
+             : stage > 0 ? (const void*)k_w3_p<T, 1, true>
+                         : (const void*)k_w3_p<T, 0, true>;
+  return stage < 0   ? (const void*)k_w3_p<T, -1, false>
+         : stage > 0 ? (const void*)k_w3_p<T, 1, false>
+                     : (const void*)k_w3_p<T, 0, false>;
 }
 
 int w3_persistent_grid(bool single, int stage, size_t lds, bool pack) {
@@ -512,9 +671,9 @@ template void launch_3d_persistent<double>(hipStream_t, int, const BatchDesc*, c
 template void launch_3d_persistent<float>(hipStream_t, int, const BatchDesc*, const WorkItem*, int,
                                           size_t, int, bool);
 template void launch_y3<double>(hipStream_t, void*, void*, int, int, int, int, int, const void*,
-                                const int*);
+                                const int*, bool);
 template void launch_y3<float>(hipStream_t, void*, void*, int, int, int, int, int, const void*,
-                               const int*);
+                               const int*, bool);
 template void launch_z3<double>(hipStream_t, void*, int, int, int, int, const double*, int, double,
                                 const void*, const int*, bool);
 template void launch_z3<float>(hipStream_t, void*, int, int, int, int, const float*, int, float,

@@ -172,14 +172,15 @@ inline int tensor3_row(int Pz, bool single) {
 }
 // ---- full 3-D path (grids with more than 4 layers) --------------------------
 // y transform of the (kx, z) planes: dir -1: A[kx][z][y][c] -> B[kx][ky][z][c];
-// dir +1: B -> A (rows y < ny kept).
+// dir +1: B -> A (rows y < ny kept).  pack: as for launch_z3.
 template <typename T>
 void launch_y3(hipStream_t s, void* A, void* B, int nz, int ny, int Py, int M, int dir,
-               const void* twy, const int* done);
+               const void* twy, const int* done, bool pack);
 // z transform of every (kx, ky) pencil of B, product with the tensor, inverse.
-// pack: short pencils share a wave (double-precision contexts; the passes of
-// a single-precision context, whose iterates amplify a last bit contracted
-// otherwise, keep one pencil per wave in both precisions)
+// pack: short pencils share a wave and the components go together
+// (double-precision contexts; the passes of a single-precision context, whose
+// iterates amplify a last bit contracted otherwise, keep one pencil per wave
+// in both precisions)
 template <typename T>
 void launch_z3(hipStream_t s, void* B, int nz, int Py, int Pz, int M, const T* T3, int rstride,
                T scale, const void* twz, const int* done, bool pack);
@@ -235,10 +236,10 @@ void launch_x_persistent(hipStream_t s, bool inverse, const BatchDesc* descs,
                          const WorkItem* items, int n_items, int threads, size_t lds, int grid);
 // 3-D path (demag3d.hip), persistent batched: stage -1 forward y, 0 z with
 // the tensor product, +1 inverse y; items = (sample, block of the stage's
-// per-sample grid: (M+1) ceil(nz/4) for y, z3_blocks for z)
+// per-sample grid: y3_blocks for y, z3_blocks for z)
 int w3_persistent_grid(bool single, int stage, size_t lds, bool pack);
 size_t w3_block_lds(bool single, int stage, int P, bool pack);
-int y3_blocks(int nz, int M);
+int y3_blocks(int nz, int Py, int M, bool pack);
 int z3_blocks(int Py, int Pz, int M, bool pack);
 template <typename T>
 void launch_3d_persistent(hipStream_t s, int stage, const BatchDesc* descs, const WorkItem* items,
