@@ -255,10 +255,21 @@ __device__ __forceinline__ double fin_wait(const FinFuse& fz) {
 
 // Body of the forward x pass for logical block L (rows z, y0 .. y0+R-1).
 // FUSE: the pass takes the previous iteration's finish over (fz.st set).
-template <typename T, int VL, bool FUSE>
+// RC: the rows per block where the kernel is compiled for them (1), else 0.
+// Both x passes are bound by the instructions a wave issues, not by memory
+// (issuing a cell's loads ahead of the spectrum's made the inverse pass 10 to
+// 35% slower), and with R at run time a third of them were divisions by 3 R
+// and nx and the 64-bit addresses of every optional output.  With one row a
+// thread keeps its place in the chunks, takes its cells from constants
+// (nx <= M: one round) and addresses them by 32-bit offsets: inverse pass at
+// M = 128 2113 -> 1279 instructions, forward 1858 -> 904.  Forward and
+// inverse: 128^3 90 and 124 -> 80 and 109 us, 400 x 200 x 4 21.9 and 22.0 ->
+// 20.7 and 20.0, mixed 20.8 and 21.6 -> 19.0 and 20.7, 200 x 100 x 2 13.8 and
+// 11.0 -> 12.5 and 10.0.
+template <typename T, int VL, bool FUSE, int RC>
 __device__ __forceinline__ void xf_w_body(double* __restrict__ m, const T* __restrict__ g,
                                           T* __restrict__ sbuf, const MinState* st, int nx,
-                                          int ny, int nz, int R, cx<T>* __restrict__ out,
+                                          int ny, int nz, int Rarg, cx<T>* __restrict__ out,
                                           const cx<T>* __restrict__ twx, int L,
                                           const double* __restrict__ msub,
                                           double* __restrict__ mcopy, const FinFuse& fz) {
@@ -284,10 +295,11 @@ __device__ __forceinline__ void xf_w_body(double* __restrict__ m, const T* __res
   extern __shared__ __align__(16) unsigned char smem[];
   cx<T>* sm = reinterpret_cast<cx<T>*>(smem);
   T* smr = reinterpret_cast<T*>(smem);
+  const int R = RC > 0 ? RC : Rarg;
   const int nyb = (ny + R - 1) / R;
   const int z = L / nyb;
   const int y0 = (L - z * nyb) * R;
-  const int rows = min(R, ny - y0);
+  const int rows = RC == 1 ? 1 : min(R, ny - y0);
   const int N = nx * ny * nz;
   const int tid = thread_index(), nthr = 192 * R;
   // the row-parallel loops take 192 R threads (a persistent launch may have
@@ -296,14 +308,15 @@ __device__ __forceinline__ void xf_w_body(double* __restrict__ m, const T* __res
   const int first = tid < nthr ? tid : (1 << 30);
   // phase 1: pending update of the rows, sequences into LDS (x = 2j + h -> re/im of j)
   {
-    constexpr int U = 4;                       // cells in flight per thread
+    // cells in flight per thread (one row: nx <= M in one round)
+    constexpr int U = RC == 1 ? (VL + 2) / 3 : 4;
     const int total = rows * nx;
     const size_t row0 = ((size_t)z * ny + y0) * nx;   // rows of the block are contiguous
     // one cell of phase 1: line-search base handling, the pending update
     // (eq. (7)) with s = m+ - m, the copy / subtraction of the reference,
     // and the sequence value into LDS
     auto cell = [&](int idx, double (&mi)[3], double (&gi)[3], bool upd, bool ls_upd) {
-      const int r = idx / nx, x = idx - r * nx;
+      const int r = RC == 1 ? 0 : idx / nx, x = idx - r * nx;
       const size_t i = row0 + idx;
       if (ls_upd) {
         // line search: the trial starts from the saved base (retry) or from
@@ -366,7 +379,7 @@ __device__ __forceinline__ void xf_w_body(double* __restrict__ m, const T* __res
         for (int u = 0; u < U; ++u) {
           const int idx = base + u * nthr;
           if (idx >= total) continue;
-          const int r = idx / nx, x = idx - r * nx;
+          const int r = RC == 1 ? 0 : idx / nx, x = idx - r * nx;
           const size_t i = row0 + idx;
           if (ls_upd) {
 #pragma unroll
@@ -458,10 +471,17 @@ __device__ __forceinline__ void xf_w_body(double* __restrict__ m, const T* __res
   if (done != 0) return;
   // zero padding x in [nx, 2M)
   const int jz = nx >> 1;   // first complex slot holding padding (its .y if nx is odd)
-  for (int idx = first; idx < rows * 3 * (M - jz); idx += nthr) {
-    const int q = idx / (M - jz), j = jz + idx - q * (M - jz);
+  auto clear = [&](int q, int j) {
     if (2 * j >= nx) sm[(size_t)q * RG + j] = mk(T(0), T(0));
     else smr[2 * ((size_t)q * RG + j) + 1] = T(0);          // x = nx - 1 even: .y is padding
+  };
+  if constexpr (RC == 1) {
+    for (int j = jz + (tid & 63); j < M; j += 64) clear(tid >> 6, j);
+  } else {
+    for (int idx = first; idx < rows * 3 * (M - jz); idx += nthr) {
+      const int q = idx / (M - jz);
+      clear(q, jz + idx - q * (M - jz));
+    }
   }
   __syncthreads();
   // phase 2: wave FFT of one (row, component)
@@ -509,25 +529,35 @@ __device__ __forceinline__ void xf_w_body(double* __restrict__ m, const T* __res
   const size_t slab = (size_t)3 * nz * ny;
   const int q3 = 3 * rows;
   cx<T>* dst = out + ((size_t)z * ny + y0) * 3;
-  for (int idx = first; idx < (M + 1) * q3; idx += nthr) {
-    const int k = idx / q3, q = idx - k * q3;
-    dst[(size_t)k * slab + q] = sm[(size_t)q * RG + wx_pad(k)];
+  if constexpr (RC == 1) {
+    // 192 threads: the same value of the chunk in every round
+    const int k0 = tid / 3, q = tid - k0 * 3;
+    const cx<T>* from = sm + (size_t)q * RG;
+    dst += (size_t)k0 * slab + q;
+#pragma unroll
+    for (int u = 0; u < VL; ++u) dst[(size_t)(64 * u) * slab] = from[wx_pad(k0 + 64 * u)];
+    if (tid < 3) dst[(size_t)M * slab] = from[wx_pad(M)];
+  } else {
+    for (int idx = first; idx < (M + 1) * q3; idx += nthr) {
+      const int k = idx / q3, q = idx - k * q3;
+      dst[(size_t)k * slab + q] = sm[(size_t)q * RG + wx_pad(k)];
+    }
   }
 }
 
-template <typename T, int VL, bool FUSE>
+template <typename T, int VL, bool FUSE, int RC>
 __global__ void __launch_bounds__(kXwThreads)
 k_xf_w(double* __restrict__ m, const T* __restrict__ g, T* __restrict__ sbuf,
        const MinState* st, int nx, int ny, int nz, int R, cx<T>* __restrict__ out,
        const cx<T>* __restrict__ twx, const double* __restrict__ msub,
        double* __restrict__ mcopy, FinFuse fz) {
-  xf_w_body<T, VL, FUSE>(m, g, sbuf, st, nx, ny, nz, R, out, twx,
+  xf_w_body<T, VL, FUSE, RC>(m, g, sbuf, st, nx, ny, nz, R, out, twx,
                          xcd_remap(blockIdx.x, gridDim.x), msub, mcopy, fz);
 }
 
 // Body of the inverse x pass with the local terms for logical block L.
-template <typename T, int VL>
-__device__ __forceinline__ void xil_w_body(const cx<T>* __restrict__ in, LocalArgs a, int R,
+template <typename T, int VL, int RC>
+__device__ __forceinline__ void xil_w_body(const cx<T>* __restrict__ in, LocalArgs a, int Rarg,
                                            double* __restrict__ Hd_out,
                                            double* __restrict__ partials,
                                            const cx<T>* __restrict__ twx, int L) {
@@ -545,10 +575,11 @@ __device__ __forceinline__ void xil_w_body(const cx<T>* __restrict__ in, LocalAr
   cx<T>* sm = reinterpret_cast<cx<T>*>(smem);
   __shared__ double scratch[kNPartial * kXwThreads / 64];
   const int nx = a.nx, ny = a.ny, nz = a.nz;
+  const int R = RC > 0 ? RC : Rarg;
   const int nyb = (ny + R - 1) / R;
   const int z = L / nyb;
   const int y0 = (L - z * nyb) * R;
-  const int rows = min(R, ny - y0);
+  const int rows = RC == 1 ? 1 : min(R, ny - y0);
   const int N = nx * ny * nz;
   const int tid = thread_index(), nthr = 192 * R;
   // the row-parallel loops take 192 R threads (a persistent launch may have
@@ -559,28 +590,48 @@ __device__ __forceinline__ void xil_w_body(const cx<T>* __restrict__ in, LocalAr
   const size_t slab = (size_t)3 * nz * ny;
   const int q3 = 3 * rows;
   const cx<T>* src = in + ((size_t)z * ny + y0) * 3;
-  {
-    constexpr int U = 8;                       // loads in flight per thread
-    const int total = (M + 1) * q3;
-    for (int base = first; base < total; base += U * nthr) {
-      T re[U], im[U];
+  if constexpr (RC == 1) {
+    // 192 threads: the same value of the chunk in every round
+    const int k0 = tid / 3, q = tid - k0 * 3;
+    cx<T>* to = sm + (size_t)q * RG;
+    src += (size_t)k0 * slab + q;
+    T re[VL + 1], im[VL + 1];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int idx = min(base + u * nthr, total - 1);
-        const int k = idx / q3, q = idx - k * q3;
-        const cx<T> v = src[(size_t)k * slab + q];
-        re[u] = v.x;
-        im[u] = v.y;
-      }
+    for (int u = 0; u < VL; ++u) {
+      const cx<T>& e = src[(size_t)(64 * u) * slab];
+      re[u] = e.x;
+      im[u] = e.y;
+    }
+    if (tid < 3) {
+      const cx<T>& e = src[(size_t)M * slab];
+      re[VL] = e.x;
+      im[VL] = e.y;
+    }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int idx = base + u * nthr;
-        if (idx < total) {
+    for (int u = 0; u < VL; ++u) to[wx_pad(k0 + 64 * u)] = mk(re[u], im[u]);
+    if (tid < 3) to[wx_pad(M)] = mk(re[VL], im[VL]);
+  } else {
+      constexpr int U = 8;                       // loads in flight per thread
+      const int total = (M + 1) * q3;
+      for (int base = first; base < total; base += U * nthr) {
+        T re[U], im[U];
+  #pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int idx = min(base + u * nthr, total - 1);
           const int k = idx / q3, q = idx - k * q3;
-          sm[(size_t)q * RG + wx_pad(k)] = mk(re[u], im[u]);
+          const cx<T> v = src[(size_t)k * slab + q];
+          re[u] = v.x;
+          im[u] = v.y;
+        }
+  #pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int idx = base + u * nthr;
+          if (idx < total) {
+            const int k = idx / q3, q = idx - k * q3;
+            sm[(size_t)q * RG + wx_pad(k)] = mk(re[u], im[u]);
+          }
         }
       }
-    }
   }
   if (done != 0) return;
   __syncthreads();
@@ -612,37 +663,25 @@ __device__ __forceinline__ void xil_w_body(const cx<T>* __restrict__ in, LocalAr
   // phase 3: local terms of the rows
   const bool bb = a.g != nullptr && a.s != nullptr && a.st != nullptr && (kst > 0 || lst != 0);
   double part[kNPartial] = {};
-  {
-    constexpr int U = 1;                       // cells per thread per round
-    const int total = rows * nx;
-    const int row0 = (z * ny + y0) * nx;
-    for (int base = first; base < total; base += U * nthr) {
-      CellIn cin[U];
+  const int cells = rows * nx;
+  const int row0 = (z * ny + y0) * nx;
+  for (int idx = first; idx < cells; idx += nthr) {
+    const int rr = RC == 1 ? 0 : idx / nx, x = idx - rr * nx;
+    const int i = row0 + idx;
+    CellIn cin;
+    fetch_cell<T>(a, i, x, y0 + rr, z, bb, cin);
+    double hd[3];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int idx = base + u * nthr;
-        if (idx < total) fetch_cell<T>(a, row0 + idx, bb, cin[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int idx = base + u * nthr;
-        if (idx >= total) continue;
-        const int rr = idx / nx, x = idx - rr * nx;
-        const int i = row0 + idx;
-        double hd[3];
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc) {
-          const cx<T> v = sm[(size_t)(rr * 3 + cc) * RG + wx_pad(x >> 1)];
-          hd[cc] = (double)((x & 1) ? v.y : v.x);
-          if (a.Hd_add != nullptr) hd[cc] += a.Hd_add[(size_t)cc * N + i];
-        }
-        if (Hd_out != nullptr) {
-#pragma unroll
-          for (int cc = 0; cc < 3; ++cc) Hd_out[(size_t)cc * N + i] = hd[cc];
-        }
-        compute_cell<T>(a, i, hd, bb, cin[u], part);
-      }
+    for (int cc = 0; cc < 3; ++cc) {
+      const cx<T> v = sm[(size_t)(rr * 3 + cc) * RG + wx_pad(x >> 1)];
+      hd[cc] = (double)((x & 1) ? v.y : v.x);
+      if (a.Hd_add != nullptr) hd[cc] += at_byte(a.Hd_add + (size_t)cc * N, (unsigned)i * 8u);
     }
+    if (Hd_out != nullptr) {
+#pragma unroll
+      for (int cc = 0; cc < 3; ++cc) put_byte(Hd_out + (size_t)cc * N, (unsigned)i * 8u, hd[cc]);
+    }
+    compute_cell<T>(a, i, hd, bb, cin, part);
   }
   bool is_max[kNPartial];
   for (int q = 0; q < kNPartial; ++q) is_max[q] = q == kPartMax;
@@ -650,11 +689,11 @@ __device__ __forceinline__ void xil_w_body(const cx<T>* __restrict__ in, LocalAr
     block_reduce_store<kXwThreads>(part, is_max, scratch, partials + (size_t)L * kNPartial);
 }
 
-template <typename T, int VL>
+template <typename T, int VL, int RC>
 __global__ void __launch_bounds__(kXwThreads)
 k_xil_w(const cx<T>* __restrict__ in, LocalArgs a, int R, double* __restrict__ Hd_out,
         double* __restrict__ partials, const cx<T>* __restrict__ twx) {
-  xil_w_body<T, VL>(in, a, R, Hd_out, partials, twx, xcd_remap(blockIdx.x, gridDim.x));
+  xil_w_body<T, VL, RC>(in, a, R, Hd_out, partials, twx, xcd_remap(blockIdx.x, gridDim.x));
 }
 
 // ---------------------------------------------------------------------------
@@ -886,7 +925,7 @@ k_xil_long(const cx<double>* __restrict__ in, LocalArgs a, double* __restrict__ 
   for (int x = tid; x < nx; x += kXlThreads) {
     const int i = L * nx + x;
     CellIn cin;
-    fetch_cell<T>(a, i, bb, cin);
+    fetch_cell<T>(a, i, x, L % a.ny, L / a.ny, bb, cin);
     double hd[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -909,23 +948,23 @@ k_xil_long(const cx<double>* __restrict__ in, LocalArgs a, double* __restrict__ 
 // items[b] names the sample and its logical block; every sample of a launch
 // has the same transform length and rows per block.
 // Logical block `block` of sample d's forward x pass.
-template <typename T, int VL>
+template <typename T, int VL, int RC>
 __device__ __forceinline__ void xf_desc(const BatchDesc& d, int block) {
   const FinFuse none{nullptr, nullptr, 0.0, 0.0, 0, 0, 0};
-  xf_w_body<T, VL, false>(d.m, static_cast<const T*>(d.g), static_cast<T*>(d.s), d.st, d.nx, d.ny,
+  xf_w_body<T, VL, false, RC>(d.m, static_cast<const T*>(d.g), static_cast<T*>(d.s), d.st, d.nx, d.ny,
                    d.nz, d.R, (cx<T>*)d.spec, (const cx<T>*)d.twx, block,
                    d.pass == 1 ? d.mref : nullptr, d.pass == 2 ? d.mref : nullptr, none);
 }
 
-template <typename T, int VL>
+template <typename T, int VL, int RC>
 __global__ void __launch_bounds__(kXwThreads)
 k_xf_wb(const BatchDesc* __restrict__ descs, const WorkItem* __restrict__ items) {
   const WorkItem it = items[blockIdx.x];
-  xf_desc<T, VL>(descs[it.sample], it.block);
+  xf_desc<T, VL, RC>(descs[it.sample], it.block);
 }
 
 // Logical block `block` of sample d's inverse x pass with its local terms.
-template <typename T, int VL>
+template <typename T, int VL, int RC>
 __device__ __forceinline__ void xil_desc(const BatchDesc& d, int block) {
   LocalArgs a;
   a.m = d.m;
@@ -959,19 +998,19 @@ __device__ __forceinline__ void xil_desc(const BatchDesc& d, int block) {
     a.g = nullptr;
     a.s = nullptr;
     a.st = nullptr;
-    xil_w_body<T, VL>((const cx<T>*)d.spec, a, d.R, d.hdref, nullptr, (const cx<T>*)d.twx,
+    xil_w_body<T, VL, RC>((const cx<T>*)d.spec, a, d.R, d.hdref, nullptr, (const cx<T>*)d.twx,
                       block);
     return;
   }
-  xil_w_body<T, VL>((const cx<T>*)d.spec, a, d.R, nullptr, d.partials, (const cx<T>*)d.twx,
+  xil_w_body<T, VL, RC>((const cx<T>*)d.spec, a, d.R, nullptr, d.partials, (const cx<T>*)d.twx,
                     block);
 }
 
-template <typename T, int VL>
+template <typename T, int VL, int RC>
 __global__ void __launch_bounds__(kXwThreads)
 k_xil_wb(const BatchDesc* __restrict__ descs, const WorkItem* __restrict__ items) {
   const WorkItem it = items[blockIdx.x];
-  xil_desc<T, VL>(descs[it.sample], it.block);
+  xil_desc<T, VL, RC>(descs[it.sample], it.block);
 }
 
 // ---- persistent batched x passes ------------------------------------------------
@@ -981,13 +1020,13 @@ k_xil_wb(const BatchDesc* __restrict__ descs, const WorkItem* __restrict__ items
 // the item's sample length.  A sample's rows per block R may be
 // below the launch's blockDim.x / 192 (the surplus waves then skip the
 // transform).
-template <typename T, bool INV>
+template <typename T, bool INV, int RC>
 __device__ __forceinline__ void x_item(const BatchDesc& d, int block) {
   switch (d.M >> 6) {
 #define MMK_X_CASE(V)                          \
   case V:                                      \
-    if (INV) xil_desc<T, V>(d, block);         \
-    else xf_desc<T, V>(d, block);              \
+    if (INV) xil_desc<T, V, RC>(d, block);     \
+    else xf_desc<T, V, RC>(d, block);          \
     break;
     MMK_X_CASE(1)
     MMK_X_CASE(2)
@@ -1002,12 +1041,12 @@ __device__ __forceinline__ void x_item(const BatchDesc& d, int block) {
   }
 }
 
-template <typename T, bool INV>
+template <typename T, bool INV, int RC>
 __global__ void __launch_bounds__(kXwThreads)
 k_x_wp(const BatchDesc* __restrict__ descs, const WorkItem* __restrict__ items, int n_items) {
   persist_loop(n_items, [&](int v) {
     const WorkItem it = items[v];
-    x_item<T, INV>(descs[it.sample], it.block);
+    x_item<T, INV, RC>(descs[it.sample], it.block);
   });
 }
 
@@ -1062,7 +1101,8 @@ static void xf_wave(hipStream_t s, double* m, const T* g, T* sbuf, const MinStat
                     double* mcopy, const FinFuse& fz) {
   const size_t lds = (size_t)3 * R * wx_region<VL>() * sizeof(cx<T>);
   const int nb = nz * ((ny + R - 1) / R);
-  auto k = fz.st != nullptr ? k_xf_w<T, VL, true> : k_xf_w<T, VL, false>;
+  auto k = fz.st != nullptr ? (R == 1 ? k_xf_w<T, VL, true, 1> : k_xf_w<T, VL, true, 0>)
+                            : (R == 1 ? k_xf_w<T, VL, false, 1> : k_xf_w<T, VL, false, 0>);
   set_lds(k, lds);
   hipLaunchKernelGGL(k, dim3(nb), dim3(192 * R), lds, s, m, g, sbuf, st, nx, ny, nz, R,
                      (cx<T>*)out, (const cx<T>*)twx, msub, mcopy, fz);
@@ -1073,7 +1113,7 @@ static void xil_wave(hipStream_t s, const void* in, const LocalArgs& a, int R, d
                      double* partials, const void* twx) {
   const size_t lds = (size_t)3 * R * wx_region<VL>() * sizeof(cx<T>);
   const int nb = a.nz * ((a.ny + R - 1) / R);
-  auto k = k_xil_w<T, VL>;
+  auto k = R == 1 ? k_xil_w<T, VL, 1> : k_xil_w<T, VL, 0>;
   set_lds(k, lds);
   hipLaunchKernelGGL(k, dim3(nb), dim3(192 * R), lds, s, (const cx<T>*)in, a, R, Hd_out, partials,
                      (const cx<T>*)twx);
@@ -1198,21 +1238,28 @@ static void xb_launch(hipStream_t s, bool inverse, const BatchDesc* descs, const
                       int n_items, int R) {
   const size_t lds = (size_t)3 * R * wx_region<VL>() * sizeof(cx<T>);
   if (inverse) {
-    auto k = k_xil_wb<T, VL>;
+    auto k = R == 1 ? k_xil_wb<T, VL, 1> : k_xil_wb<T, VL, 0>;
     set_lds(k, lds);
     hipLaunchKernelGGL(k, dim3(n_items), dim3(192 * R), lds, s, descs, items);
   } else {
-    auto k = k_xf_wb<T, VL>;
+    auto k = R == 1 ? k_xf_wb<T, VL, 1> : k_xf_wb<T, VL, 0>;
     set_lds(k, lds);
     hipLaunchKernelGGL(k, dim3(n_items), dim3(192 * R), lds, s, descs, items);
   }
 }
 
+// the persistent kernel of a launch of `threads` = 192 R per block
+template <typename T>
+static const void* x_wp_kernel(bool inverse, int threads) {
+  if (threads == 192)
+    return inverse ? (const void*)k_x_wp<T, true, 1> : (const void*)k_x_wp<T, false, 1>;
+  return inverse ? (const void*)k_x_wp<T, true, 0> : (const void*)k_x_wp<T, false, 0>;
+}
+
 // Blocks of a persistent x launch that stay resident together (a multiple
 // of 8, at least 8).
 int x_persistent_grid(bool single, bool inverse, int threads, size_t lds) {
-  const void* k = single ? (inverse ? (const void*)k_x_wp<float, true> : (const void*)k_x_wp<float, false>)
-                         : (inverse ? (const void*)k_x_wp<double, true> : (const void*)k_x_wp<double, false>);
+  const void* k = single ? x_wp_kernel<float>(inverse, threads) : x_wp_kernel<double>(inverse, threads);
   if (lds > 48 * 1024) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   int per_cu = 0, dev = 0, cus = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, threads, lds) != hipSuccess ||
@@ -1230,15 +1277,10 @@ void launch_x_persistent(hipStream_t s, bool inverse, const BatchDesc* descs,
                          const WorkItem* items, int n_items, int threads, size_t lds, int grid) {
   const int g = n_items < grid ? n_items : grid;
   if (g <= 0) return;
-  if (inverse) {
-    auto k = k_x_wp<T, true>;
-    set_lds(k, lds);
-    hipLaunchKernelGGL(k, dim3(g), dim3(threads), lds, s, descs, items, n_items);
-  } else {
-    auto k = k_x_wp<T, false>;
-    set_lds(k, lds);
-    hipLaunchKernelGGL(k, dim3(g), dim3(threads), lds, s, descs, items, n_items);
-  }
+  const void* k = x_wp_kernel<T>(inverse, threads);
+  if (lds > 48 * 1024) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  void* args[] = {(void*)&descs, (void*)&items, (void*)&n_items};
+  (void)hipLaunchKernel(k, dim3(g), dim3(threads), args, lds, s);
 }
 
 size_t x_block_lds(bool single, int M, int R) {

@@ -386,17 +386,27 @@ __device__ __forceinline__ double dpp_f64(double old, double v) {
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
+// The same with zero for lanes without a source (every row enabled): no
+// register to clear first.
+template <int CTRL>
+__device__ __forceinline__ double dpp0_f64(double v) {
+  const long long x = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
 // Wave total in lane 63: an inclusive scan within each row of 16 lanes
 // (row_shr 1, 2, 4, 8: lane 15 of a row holds the row's total), then row 0's
 // total into row 1 and row 2's into row 3 (row_bcast 15), then lane 31's
 // into rows 2 and 3 (row_bcast 31).  No LDS traffic.
 __device__ __forceinline__ double wave_sum(double v) {
-  v += dpp_f64<0x111>(0.0, v);
-  v += dpp_f64<0x112>(0.0, v);
-  v += dpp_f64<0x114>(0.0, v);
-  v += dpp_f64<0x118>(0.0, v);
-  v += dpp_f64<0x142, 0xa>(0.0, v);
-  v += dpp_f64<0x143, 0xc>(0.0, v);
+  v += dpp0_f64<0x111>(v);
+  v += dpp0_f64<0x112>(v);
+  v += dpp0_f64<0x114>(v);
+  v += dpp0_f64<0x118>(v);
+  v += dpp0_f64<0x142>(v);
+  v += dpp0_f64<0x143>(v);
   return v;
 }
 __device__ __forceinline__ double wave_max(double v) {

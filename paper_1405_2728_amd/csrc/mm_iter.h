@@ -20,13 +20,24 @@ struct CellIn {
   double ku;
 };
 
-// G: the type of the g and s streams (the transform type of the kernel).
+// The double or G at a 32-bit byte offset of a block-uniform base: one vector
+// register of address instead of two (grids hold fewer than 2^29 cells, their
+// padded spectrum would not fit the device otherwise).
 template <typename G>
-__device__ __forceinline__ void fetch_cell(const LocalArgs& a, int i, bool bb, CellIn& d) {
+__device__ __forceinline__ G at_byte(const G* p, unsigned byte) {
+  return *reinterpret_cast<const G*>(reinterpret_cast<const char*>(p) + byte);
+}
+template <typename G>
+__device__ __forceinline__ void put_byte(G* p, unsigned byte, G v) {
+  *reinterpret_cast<G*>(reinterpret_cast<char*>(p) + byte) = v;
+}
+
+// Cell i = (x, y, z).  G: the type of the g and s streams (the transform type
+// of the kernel).
+template <typename G>
+__device__ __forceinline__ void fetch_cell(const LocalArgs& a, int i, int x, int y, int z, bool bb,
+                                           CellIn& d) {
   const int N = a.nx * a.ny * a.nz;
-  const int x = i % a.nx;
-  const int y = (i / a.nx) % a.ny;
-  const int z = i / (a.nx * a.ny);
   const int sy = a.nx, sz = a.nx * a.ny;
   const int j[6] = {x > 0 ? i - 1 : i,        x < a.nx - 1 ? i + 1 : i,
                     y > 0 ? i - sy : i,       y < a.ny - 1 ? i + sy : i,
@@ -34,10 +45,10 @@ __device__ __forceinline__ void fetch_cell(const LocalArgs& a, int i, bool bb, C
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     const double* mc = a.m + (size_t)c * N;
-    const double m0 = mc[i];
+    const double m0 = at_byte(mc, (unsigned)i * 8u);
     double nb[6];
 #pragma unroll
-    for (int q = 0; q < 6; ++q) nb[q] = mc[j[q]];
+    for (int q = 0; q < 6; ++q) nb[q] = at_byte(mc, (unsigned)j[q] * 8u);
     d.m[c] = m0;
     d.hex[c] = a.cx * ((nb[0] - m0) + (nb[1] - m0)) + a.cy * ((nb[2] - m0) + (nb[3] - m0)) +
                a.cz * ((nb[4] - m0) + (nb[5] - m0));
@@ -45,13 +56,14 @@ __device__ __forceinline__ void fetch_cell(const LocalArgs& a, int i, bool bb, C
   if (a.g != nullptr) {
     const G* gp = static_cast<const G*>(a.g);
     const G* sp = static_cast<const G*>(a.s);
+    const unsigned o = (unsigned)i * (unsigned)sizeof(G);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      d.g[c] = bb ? (double)gp[(size_t)c * N + i] : 0.0;
-      d.s[c] = bb ? (double)sp[(size_t)c * N + i] : 0.0;
+      d.g[c] = bb ? (double)at_byte(gp + (size_t)c * N, o) : 0.0;
+      d.s[c] = bb ? (double)at_byte(sp + (size_t)c * N, o) : 0.0;
     }
   }
-  d.ku = a.ku_map != nullptr ? a.ku_map[i] : a.ku;
+  d.ku = a.ku_map != nullptr ? at_byte(a.ku_map, (unsigned)i * 8u) : a.ku;
 }
 
 // Local terms of one cell i given its demag field hd: H_eff, g = m x (m x H)
@@ -63,6 +75,7 @@ template <typename G>
 __device__ __forceinline__ void compute_cell(const LocalArgs& a, int i, const double hd[3],
                                              bool bb, const CellIn& d, double part[kNPartial]) {
   const int N = a.nx * a.ny * a.nz;
+  const unsigned o8 = (unsigned)i * 8u;
   const double* hex = d.hex;
   const double* mi = d.m;
   const double mu = mi[0] * a.u[0] + mi[1] * a.u[1] + mi[2] * a.u[2];
@@ -75,15 +88,15 @@ __device__ __forceinline__ void compute_cell(const LocalArgs& a, int i, const do
   }
   if (a.Hout != nullptr) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) a.Hout[(size_t)c * N + i] = h[c];
+    for (int c = 0; c < 3; ++c) put_byte(a.Hout + (size_t)c * N, o8, h[c]);
   }
   if (a.Hex_out != nullptr) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) a.Hex_out[(size_t)c * N + i] = hex[c];
+    for (int c = 0; c < 3; ++c) put_byte(a.Hex_out + (size_t)c * N, o8, hex[c]);
   }
   if (a.Han_out != nullptr) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) a.Han_out[(size_t)c * N + i] = han[c];
+    for (int c = 0; c < 3; ++c) put_byte(a.Han_out + (size_t)c * N, o8, han[c]);
   }
   part[3] += mi[0] * hd[0] + mi[1] * hd[1] + mi[2] * hd[2];
   part[4] += mi[0] * hex[0] + mi[1] * hex[1] + mi[2] * hex[2];
@@ -109,9 +122,10 @@ __device__ __forceinline__ void compute_cell(const LocalArgs& a, int i, const do
       part[2] += y0 * y0 + y1 * y1 + y2 * y2;
     }
     G* go = static_cast<G*>(a.g_out != nullptr ? a.g_out : a.g);
-    go[i] = (G)g0;
-    go[(size_t)N + i] = (G)g1;
-    go[2 * (size_t)N + i] = (G)g2;
+    const unsigned o = (unsigned)i * (unsigned)sizeof(G);
+    put_byte(go, o, (G)g0);
+    put_byte(go + (size_t)N, o, (G)g1);
+    put_byte(go + 2 * (size_t)N, o, (G)g2);
   }
 }
 
@@ -119,7 +133,8 @@ template <typename G>
 __device__ __forceinline__ void local_cell(const LocalArgs& a, int i, const double hd[3],
                                            bool bb, double part[kNPartial]) {
   CellIn d;
-  fetch_cell<G>(a, i, bb, d);
+  const int x = i % a.nx, y = (i / a.nx) % a.ny, z = i / (a.nx * a.ny);
+  fetch_cell<G>(a, i, x, y, z, bb, d);
   compute_cell<G>(a, i, hd, bb, d, part);
 }
 
