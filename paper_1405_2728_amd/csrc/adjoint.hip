@@ -92,6 +92,8 @@ k_cg_start(const double* __restrict__ partials, int nb, CGState* __restrict__ cg
   cg->k = 0;
   cg->max_iter = max_iter;
   cg->alpha = cg->beta = cg->pAp = 0.0;
+  cg->bad = 0;
+  cg->rr2[0] = cg->rr2[1] = v[0];
   cg->done = !isfinite(v[0]) ? -1 : (v[0] == 0.0 ? 1 : (max_iter <= 0 ? 2 : 0));
 }
 
@@ -177,6 +179,106 @@ k_cg_direction(const double* __restrict__ m, const double* __restrict__ r,
   load3(m, N, i, mi);
   load3(r, N, i, ri);
   load3(p, N, i, pi);
+  for (int c = 0; c < 3; ++c) pi[c] = ri[c] + beta * pi[c];
+  const double mp = dot3(mi, pi);
+  for (int c = 0; c < 3; ++c) pi[c] -= mp * mi[c];
+  store3(p, N, i, pi);
+}
+
+// The same step in two kernels: every block forms alpha (or beta) from the
+// partial sums itself, in the order of the one-block kernels, while its own
+// loads are in flight.  A one-block kernel costs its launch, a boundary and a
+// round trip whatever it sums (about 3 us); a block's own sum costs nb / 256
+// loads per thread, so this form serves grids of up to kCgOwnSums partial
+// sums.  Nothing that a block reads is written in the same kernel: the two
+// sums have their own buffers, |r|^2 alternates between two places, and a
+// breakdown is noted in `bad` and becomes `done` one kernel later.
+// 200 x 100 x 2, 8 -> 6 kernels per iteration: solve and gradients 2237 -> 1865 us.
+constexpr int kCgOwnSums = 512;
+
+// the block's copy of sum(partials), in every thread
+__device__ __forceinline__ double block_total(const double* __restrict__ partials, int nb) {
+  __shared__ double total;
+  double v[1];
+  sum_partials<1>(partials, nb, v);
+  if (threadIdx.x == 0) total = v[0];
+  __syncthreads();
+  return total;
+}
+
+__global__ void __launch_bounds__(kAdjThreads)
+k_cg_update_own(double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
+                const double* __restrict__ Ap, int N, CGState* __restrict__ cg,
+                const double* __restrict__ pap_partials, int nb, double* __restrict__ rr_partials,
+                int par) {
+  if (cg->done != 0) return;         // written by k_cg_direction_own only
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  double xv[3] = {}, rv[3] = {}, pv[3] = {}, av[3] = {};
+  if (i < N) {
+    load3(x, N, i, xv);
+    load3(r, N, i, rv);
+    load3(p, N, i, pv);
+    load3(Ap, N, i, av);
+  }
+  const double rr = cg->rr2[par];
+  const double pAp = block_total(pap_partials, nb);
+  // a non-positive curvature means m is not a strict local minimum
+  const bool bad = !(pAp > 0.0) || !isfinite(pAp);
+  const double alpha = rr / pAp;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    cg->pAp = pAp;
+    cg->bad = bad ? 1 : 0;
+    if (!bad) cg->alpha = alpha;
+  }
+  if (bad) return;
+  double part[1] = {0.0};
+  if (i < N) {
+    for (int c = 0; c < 3; ++c) {
+      xv[c] += alpha * pv[c];
+      rv[c] = rv[c] - alpha * av[c];
+      part[0] += rv[c] * rv[c];
+    }
+    store3(x, N, i, xv);
+    store3(r, N, i, rv);
+  }
+  write_partials<1>(part, rr_partials);
+}
+
+__global__ void __launch_bounds__(kAdjThreads)
+k_cg_direction_own(const double* __restrict__ m, const double* __restrict__ r,
+                   double* __restrict__ p, int N, CGState* __restrict__ cg,
+                   const double* __restrict__ rr_partials, int nb, int par) {
+  // block 0 sets done below: thread 0 reads it for its whole block
+  __shared__ int s_done;
+  if (threadIdx.x == 0) s_done = cg->done;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  double mi[3] = {}, ri[3] = {}, pi[3] = {};
+  if (i < N) {
+    load3(m, N, i, mi);
+    load3(r, N, i, ri);
+    load3(p, N, i, pi);
+  }
+  const double rr = cg->rr2[par];
+  const int bad = cg->bad;
+  const double rr_new = block_total(rr_partials, nb);
+  if (s_done != 0) return;
+  const double beta = rr_new / rr;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (bad) {
+      cg->done = -1;
+    } else {
+      const long long k = cg->k + 1;
+      cg->k = k;
+      cg->beta = beta;
+      cg->rr = rr_new;
+      cg->rr2[par ^ 1] = rr_new;
+      if (!isfinite(rr_new)) cg->done = -1;
+      else if (rr_new <= cg->tol2 * cg->bb) cg->done = 1;
+      else if (k >= cg->max_iter) cg->done = 2;
+    }
+  }
+  if (bad || i >= N) return;
+  // (after the last iteration p is not read again)
   for (int c = 0; c < 3; ++c) pi[c] = ri[c] + beta * pi[c];
   const double mp = dot3(mi, pi);
   for (int c = 0; c < 3; ++c) pi[c] -= mp * mi[c];
@@ -276,8 +378,16 @@ void launch_project(hipStream_t s, const double* m, const double* v, double* out
 }
 
 void launch_cg_step(hipStream_t s, const double* m, double* x, double* r, double* p,
-                    const double* Ap, int N, double* partials, CGState* cg) {
+                    const double* Ap, int N, double* partials, CGState* cg, int par) {
   const int nb = adj_blocks(N);
+  if (nb <= kCgOwnSums) {
+    double* rr_partials = partials + nb;     // partials holds five sums per block
+    hipLaunchKernelGGL(k_cg_update_own, dim3(nb), dim3(kAdjThreads), 0, s, x, r, p, Ap, N, cg,
+                       partials, nb, rr_partials, par);
+    hipLaunchKernelGGL(k_cg_direction_own, dim3(nb), dim3(kAdjThreads), 0, s, m, r, p, N, cg,
+                       rr_partials, nb, par);
+    return;
+  }
   hipLaunchKernelGGL(k_cg_alpha, dim3(1), dim3(kAdjThreads), 0, s, partials, nb, cg);
   hipLaunchKernelGGL(k_cg_update, dim3(nb), dim3(kAdjThreads), 0, s, x, r, p, Ap, N, cg, partials);
   hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(kAdjThreads), 0, s, partials, nb, cg);

@@ -2534,11 +2534,11 @@ int mm_adjoint_solve(mm_ctx* c, int sample, const double* m, const double* rhs, 
   launch_cg_init(st, m, rhs, lam, s.cr, s.cp, s.N, s.partials, s.cg, tol, (long long)max_iter);
   const double cH = kMu0Host * s.Ms * s.V;
   const int* done = &s.cg->done;
-  for (;;) {
-    for (int q = 0; q < c->poll_every; ++q) {
+  for (int par = 0;;) {                // parity of the iteration
+    for (int q = 0; q < c->poll_every; ++q, par ^= 1) {
       enqueue_hlin(c, s, s.cp, done);
       launch_hess_apply(st, m, s.Hm, s.Hlin, s.cp, s.cAp, s.N, cH, s.partials, done);
-      launch_cg_step(st, m, lam, s.cr, s.cp, s.cAp, s.N, s.partials, s.cg);
+      launch_cg_step(st, m, lam, s.cr, s.cp, s.cAp, s.N, s.partials, s.cg, par);
     }
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemcpyAsync(s.cg_host, s.cg, sizeof(CGState), hipMemcpyDeviceToHost, st));

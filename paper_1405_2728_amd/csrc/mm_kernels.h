@@ -105,6 +105,8 @@ struct CGState {
   double tol2;         // stop when rr <= tol2 bb
   long long k, max_iter;
   int done;            // 0 running; 1 converged; 2 max_iter; -1 breakdown or non-finite
+  int bad;             // breakdown found by this iteration's update
+  double rr2[2];       // |r_k|^2 by the parity of k (iterations of two kernels)
 };
 
 // One sample of a batched launch (device table): its buffers, sizes and
@@ -342,7 +344,7 @@ void launch_hess_apply(hipStream_t s, const double* m, const double* Hm, const d
                        const double* v, double* out, int N, double c, double* partials,
                        const int* done);
 void launch_cg_step(hipStream_t s, const double* m, double* x, double* r, double* p,
-                    const double* Ap, int N, double* partials, CGState* cg);
+                    const double* Ap, int N, double* partials, CGState* cg, int par);
 void launch_project(hipStream_t s, const double* m, const double* v, double* out, int N);
 void launch_param_grads(hipStream_t s, const double* m, const double* lam, const double* Hd,
                         const double* Hex1, const double H[3], const double u[3], double V,
