@@ -545,14 +545,26 @@ __device__ __forceinline__ void xf_w_body(double* __restrict__ m, const T* __res
   }
 }
 
-template <typename T, int VL, bool FUSE, int RC>
+// one row per block
+template <typename T, int VL, bool FUSE>
 __global__ void __launch_bounds__(kXwThreads)
 k_xf_w(double* __restrict__ m, const T* __restrict__ g, T* __restrict__ sbuf,
        const MinState* st, int nx, int ny, int nz, int R, cx<T>* __restrict__ out,
        const cx<T>* __restrict__ twx, const double* __restrict__ msub,
        double* __restrict__ mcopy, FinFuse fz) {
-  xf_w_body<T, VL, FUSE, RC>(m, g, sbuf, st, nx, ny, nz, R, out, twx,
-                         xcd_remap(blockIdx.x, gridDim.x), msub, mcopy, fz);
+  xf_w_body<T, VL, FUSE, 1>(m, g, sbuf, st, nx, ny, nz, R, out, twx,
+                            xcd_remap(blockIdx.x, gridDim.x), msub, mcopy, fz);
+}
+
+// R rows per block
+template <typename T, int VL, bool FUSE>
+__global__ void __launch_bounds__(kXwThreads)
+k_xf_wr(double* __restrict__ m, const T* __restrict__ g, T* __restrict__ sbuf,
+        const MinState* st, int nx, int ny, int nz, int R, cx<T>* __restrict__ out,
+        const cx<T>* __restrict__ twx, const double* __restrict__ msub,
+        double* __restrict__ mcopy, FinFuse fz) {
+  xf_w_body<T, VL, FUSE, 0>(m, g, sbuf, st, nx, ny, nz, R, out, twx,
+                            xcd_remap(blockIdx.x, gridDim.x), msub, mcopy, fz);
 }
 
 // Body of the inverse x pass with the local terms for logical block L.
@@ -689,11 +701,20 @@ __device__ __forceinline__ void xil_w_body(const cx<T>* __restrict__ in, LocalAr
     block_reduce_store<kXwThreads>(part, is_max, scratch, partials + (size_t)L * kNPartial);
 }
 
-template <typename T, int VL, int RC>
+// one row per block
+template <typename T, int VL>
 __global__ void __launch_bounds__(kXwThreads)
 k_xil_w(const cx<T>* __restrict__ in, LocalArgs a, int R, double* __restrict__ Hd_out,
         double* __restrict__ partials, const cx<T>* __restrict__ twx) {
-  xil_w_body<T, VL, RC>(in, a, R, Hd_out, partials, twx, xcd_remap(blockIdx.x, gridDim.x));
+  xil_w_body<T, VL, 1>(in, a, R, Hd_out, partials, twx, xcd_remap(blockIdx.x, gridDim.x));
+}
+
+// R rows per block
+template <typename T, int VL>
+__global__ void __launch_bounds__(kXwThreads)
+k_xil_wr(const cx<T>* __restrict__ in, LocalArgs a, int R, double* __restrict__ Hd_out,
+         double* __restrict__ partials, const cx<T>* __restrict__ twx) {
+  xil_w_body<T, VL, 0>(in, a, R, Hd_out, partials, twx, xcd_remap(blockIdx.x, gridDim.x));
 }
 
 // ---------------------------------------------------------------------------
@@ -1101,8 +1122,8 @@ static void xf_wave(hipStream_t s, double* m, const T* g, T* sbuf, const MinStat
                     double* mcopy, const FinFuse& fz) {
   const size_t lds = (size_t)3 * R * wx_region<VL>() * sizeof(cx<T>);
   const int nb = nz * ((ny + R - 1) / R);
-  auto k = fz.st != nullptr ? (R == 1 ? k_xf_w<T, VL, true, 1> : k_xf_w<T, VL, true, 0>)
-                            : (R == 1 ? k_xf_w<T, VL, false, 1> : k_xf_w<T, VL, false, 0>);
+  auto k = fz.st != nullptr ? (R == 1 ? k_xf_w<T, VL, true> : k_xf_wr<T, VL, true>)
+                            : (R == 1 ? k_xf_w<T, VL, false> : k_xf_wr<T, VL, false>);
   set_lds(k, lds);
   hipLaunchKernelGGL(k, dim3(nb), dim3(192 * R), lds, s, m, g, sbuf, st, nx, ny, nz, R,
                      (cx<T>*)out, (const cx<T>*)twx, msub, mcopy, fz);
@@ -1113,7 +1134,7 @@ static void xil_wave(hipStream_t s, const void* in, const LocalArgs& a, int R, d
                      double* partials, const void* twx) {
   const size_t lds = (size_t)3 * R * wx_region<VL>() * sizeof(cx<T>);
   const int nb = a.nz * ((a.ny + R - 1) / R);
-  auto k = R == 1 ? k_xil_w<T, VL, 1> : k_xil_w<T, VL, 0>;
+  auto k = R == 1 ? k_xil_w<T, VL> : k_xil_wr<T, VL>;
   set_lds(k, lds);
   hipLaunchKernelGGL(k, dim3(nb), dim3(192 * R), lds, s, (const cx<T>*)in, a, R, Hd_out, partials,
                      (const cx<T>*)twx);
