@@ -17,6 +17,9 @@
 //   y3 inverse  B -> A, rows y < ny kept; the real-input columns kx = 0 and
 //               kx = M store imaginary part 0
 //
+// In double-precision contexts a wave takes 512 / P planes or pencils instead
+// of one, the three components together (the _pk kernels).
+//
 // Tensor T3[kx][ky'][kz'][6] (xx, yy, zz, xy, xz, yz), ky' <= Py/2,
 // kz' <= Pz/2: the cell tensor is even in every axis for the diagonal
 // entries and odd in the two axes an off-diagonal entry names, so its
