@@ -15,6 +15,7 @@
 // Only the octant of non-negative offsets is computed; the other octants
 // follow from the parities (xy odd in X and Y, xz odd in X and Z, yz odd in
 // Y and Z, diagonal even).
+#include "mm_bands.h"
 #include "mm_device.h"
 #include "mm_kernels.h"
 
@@ -233,22 +234,21 @@ k_newell_near(double* __restrict__ out, int nx, int ny, int nz, int bx, int by, 
   const int j = (int)((q / bx) % by);
   const int k = (int)(q / ((long long)bx * by));
   const double X = i * dx, Y = j * dy, Z = k * dz;
-  const double h = fmax(dx, fmax(dy, dz));
-  const double r2 = X * X + Y * Y + Z * Z;
-  if (r2 >= 1600.0 * h * h) return;
+  const Band band = offset_band(X, Y, Z, fmax(dx, fmax(dy, dz)));
+  if (band == kBand3) return;
   const double sx = (lane & 1) ? -1.0 : 1.0, sy = (lane & 2) ? -1.0 : 1.0,
                sz = (lane & 4) ? -1.0 : 1.0;
   double v[6] = {0, 0, 0, 0, 0, 0};
   double f = -1.0;
-  if (r2 < 36.0 * h * h) {
+  if (band == kBandClosed) {
     f = 1.0;
     if (lane < 27) newell_point(lane, X, Y, Z, dx, dy, dz, v);
-  } else if (r2 < 256.0 * h * h) {
+  } else if (band == kBand6) {
     far_nodes<6>(X, Y, Z, dx, dy, dz, rl.x, rl.w, sx, sy, sz, lane >> 3, v);
   } else {
     far_nodes<4>(X, Y, Z, dx, dy, dz, rl.x + 6, rl.w + 6, sx, sy, sz, lane >> 3, v);
   }
-  if (r2 < 36.0 * h * h) {
+  if (band == kBandClosed) {
     // second differences along z, then y, then x (the points' weights are
     // the products of the axes'): each difference cancels before the next
     // axis adds to it
@@ -293,8 +293,8 @@ k_newell_far(double* __restrict__ out, int nx, int ny, int nz, double dx, double
   const int j = (int)((idx / nx) % ny);
   const int k = (int)(idx / ((long long)nx * ny));
   const double X = i * dx, Y = j * dy, Z = k * dz;
-  const double h = fmax(dx, fmax(dy, dz));
-  if (X * X + Y * Y + Z * Z < 1600.0 * h * h) return;   // the same for the offset's 8 lanes
+  // the same for the offset's 8 lanes
+  if (offset_band(X, Y, Z, fmax(dx, fmax(dy, dz))) != kBand3) return;
   double v[6] = {0, 0, 0, 0, 0, 0};
   double tx[3], ty[3], tz[3], wx[3], wy[3], wz[3];
 #pragma unroll
