@@ -182,73 +182,97 @@ __device__ __forceinline__ void far_axis(double xi, double wi, double d, double&
   w = 0.5 * d * wi * (d - t);
 }
 
+// A node of a rule on one axis: offset and tent weight.
+struct alignas(16) Node {
+  double t, w;
+};
+
 // Nodes first, first + 8, ... of the NP^3 nodes of one octant (signs sx, sy,
 // sz) of the tent-weighted Gauss-Legendre rule.
 template <int NP>
-__device__ __forceinline__ void far_nodes(double X, double Y, double Z, double dx, double dy,
-                                          double dz, const double* __restrict__ xi,
-                                          const double* __restrict__ wi, double sx, double sy,
+__device__ __forceinline__ void far_nodes(double X, double Y, double Z, const Node* ax,
+                                          const Node* ay, const Node* az, double sx, double sy,
                                           double sz, int first, double acc[6]) {
+  int a = 0, b = first / NP, c = first % NP;
   for (int n = first; n < NP * NP * NP; n += 8) {
-    const int a = n / (NP * NP), b = (n / NP) % NP, c = n % NP;
-    double tx, ty, tz, wx, wy, wz;
-    far_axis(xi[a], wi[a], dx, tx, wx);
-    far_axis(xi[b], wi[b], dy, ty, wy);
-    far_axis(xi[c], wi[c], dz, tz, wz);
-    far_node(X + sx * tx, Y + sy * ty, Z + sz * tz, wx * wy * wz, acc);
+    const Node qx = ax[a], qy = ay[b], qz = az[c];
+    far_node(X + sx * qx.t, Y + sy * qy.t, Z + sz * qz.t, qx.w * qy.w * qz.w, acc);
+    c += 8 % NP;
+    b += 8 / NP;
+    if (c >= NP) {
+      c -= NP;
+      b += 1;
+    }
+    if (b >= NP) {
+      b -= NP;
+      a += 1;
+    }
   }
 }
 
-// The rules' nodes and weights in LDS (indexed by lane-dependent nodes).
+// The 3-point rule in LDS (indexed by lane-dependent nodes).
 struct RuleLds {
-  double x[13], w[13];   // 6 points at 0, 4 at 6, 3 at 10
+  double x[3], w[3];
 };
 __device__ __forceinline__ void load_rules(const GaussRules& gr, RuleLds& r) {
   const int t = threadIdx.x;
-  if (t < 13) {
-    r.x[t] = t < 6 ? gr.x6[t] : t < 10 ? gr.x4[t - 6] : gr.x3[t - 10];
-    r.w[t] = t < 6 ? gr.w6[t] : t < 10 ? gr.w4[t - 6] : gr.w3[t - 10];
+  if (t < 3) {
+    r.x[t] = gr.x3[t];
+    r.w[t] = gr.w3[t];
   }
   __syncthreads();
 }
 
-// Offsets below 40 h (closed form, 6- and 4-point rules): one wave per offset
-// of the box bx x by x bz that holds them all, its lanes sharing the 27
-// points or the 8 NP^3 nodes.  Offsets beyond 40 h: 8 lanes per offset, one
-// per octant of the 3-point rule's nodes.  Bound by the serial chain of
-// transcendental functions, square roots and divisions of one offset: with
-// one thread per offset (162 closed-form evaluations, up to 1728 nodes in a
-// row) the 200 x 100 x 2 film took 800 us and the 128^3 cube 1359 us; split
-// they take 21 + 14 us and 74 + 592 us (the cube's 453 M far nodes at 108
-// instructions each before, the reciprocal square root and the unrolled
-// nodes halving that).
+// Offsets below 40 h.  The first ncb blocks take the closed form: a wave per
+// two offsets of the box cx x cy x cz that holds those below 6 h, 27 lanes
+// each for the 27 points.  The other blocks take the 6- and 4-point rules: a
+// wave per offset of the box bx x by x bz that holds those below 40 h, its
+// lanes sharing the 8 NP^3 nodes, whose offsets and weights per axis the block
+// forms once.  Offsets beyond 40 h: 8 lanes per offset, one per octant of the
+// 3-point rule's nodes.  Bound by the serial chain of transcendental
+// functions, square roots and divisions of one offset: with one thread per
+// offset (162 closed-form evaluations, up to 1728 nodes in a row) the
+// 200 x 100 x 2 film took 800 us and the 128^3 cube 1359 us; split they take
+// 17 + 14 us and 64 + 586 us (the cube's 453 M far nodes took 108
+// instructions each before the reciprocal square root and the unrolled nodes
+// halved that).  Flat cells, whose near band is the whole film, are
+// bound by instructions instead: 1000 x 1000 x 1 cells of 1 x 1 x 60 took
+// 3266 us with a thread per offset, 3680 with a wave for every closed form and
+// a division per node, 3050 now; 128 x 128 x 32 cells of 1 x 1 x 20 1430, 1740
+// and 1390.
 __global__ void __launch_bounds__(256)
-k_newell_near(double* __restrict__ out, int nx, int ny, int nz, int bx, int by, int bz, double dx,
-              double dy, double dz, GaussRules gr) {
-  __shared__ RuleLds rl;
-  load_rules(gr, rl);
-  const long long q = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (q >= (long long)bx * by * bz) return;
+k_newell_near(double* __restrict__ out, int nx, int ny, int nz, int ncb, int cx, int cy, int cz,
+              int bx, int by, int bz, double dx, double dy, double dz, GaussRules gr) {
+  __shared__ Node nodes[3][10];               // per axis: 6 points, then 4
+  if (threadIdx.x < 30) {
+    const int ax = threadIdx.x / 10, q = threadIdx.x % 10;
+    const double d = ax == 0 ? dx : ax == 1 ? dy : dz;
+    far_axis(q < 6 ? gr.x6[q] : gr.x4[q - 6], q < 6 ? gr.w6[q] : gr.w4[q - 6], d,
+             nodes[ax][q].t, nodes[ax][q].w);
+  }
+  __syncthreads();
+  const bool closed = (int)blockIdx.x < ncb;
   const int lane = threadIdx.x & 63;
+  long long q = (long long)((int)blockIdx.x - (closed ? 0 : ncb)) * 4 + (threadIdx.x >> 6);
+  if (closed) {
+    q = 2 * q + (lane >> 5);
+    bx = cx;
+    by = cy;
+    bz = cz;
+  }
   const int i = (int)(q % bx);
   const int j = (int)((q / bx) % by);
   const int k = (int)(q / ((long long)bx * by));
   const double X = i * dx, Y = j * dy, Z = k * dz;
   const Band band = offset_band(X, Y, Z, fmax(dx, fmax(dy, dz)));
-  if (band == kBand3) return;
-  const double sx = (lane & 1) ? -1.0 : 1.0, sy = (lane & 2) ? -1.0 : 1.0,
-               sz = (lane & 4) ? -1.0 : 1.0;
+  // a closed-form wave goes on for either of its offsets
+  const bool mine = k < bz && (band == kBandClosed) == closed && band != kBand3;
+  if (!closed && !mine) return;
   double v[6] = {0, 0, 0, 0, 0, 0};
-  double f = -1.0;
-  if (band == kBandClosed) {
-    f = 1.0;
-    if (lane < 27) newell_point(lane, X, Y, Z, dx, dy, dz, v);
-  } else if (band == kBand6) {
-    far_nodes<6>(X, Y, Z, dx, dy, dz, rl.x, rl.w, sx, sy, sz, lane >> 3, v);
-  } else {
-    far_nodes<4>(X, Y, Z, dx, dy, dz, rl.x + 6, rl.w + 6, sx, sy, sz, lane >> 3, v);
-  }
-  if (band == kBandClosed) {
+  const double f = closed ? 1.0 : -1.0;
+  if (closed) {
+    const int point = lane & 31;
+    if (mine && point < 27) newell_point(point, X, Y, Z, dx, dy, dz, v);
     // second differences along z, then y, then x (the points' weights are
     // the products of the axes'): each difference cancels before the next
     // axis adds to it
@@ -260,7 +284,14 @@ k_newell_near(double* __restrict__ out, int nx, int ny, int nz, int bx, int by, 
         v[c] = (0.5 * a + v[c]) + (0.5 * a + b);
       }
     }
+    if (!mine || point != 0) return;
   } else {
+    const double sx = (lane & 1) ? -1.0 : 1.0, sy = (lane & 2) ? -1.0 : 1.0,
+                 sz = (lane & 4) ? -1.0 : 1.0;
+    if (band == kBand6)
+      far_nodes<6>(X, Y, Z, nodes[0], nodes[1], nodes[2], sx, sy, sz, lane >> 3, v);
+    else
+      far_nodes<4>(X, Y, Z, nodes[0] + 6, nodes[1] + 6, nodes[2] + 6, sx, sy, sz, lane >> 3, v);
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
       v[c] += __shfl_xor(v[c], 32);
@@ -270,13 +301,12 @@ k_newell_near(double* __restrict__ out, int nx, int ny, int nz, int bx, int by, 
       v[c] += __shfl_xor(v[c], 2);
       v[c] += __shfl_xor(v[c], 1);
     }
+    if (lane != 0) return;
   }
-  if (lane == 0) {
-    const long long n = (long long)nx * ny * nz;
-    const long long idx = ((long long)k * ny + j) * nx + i;
-    const double kf = f / (4.0 * 3.14159265358979323846 * dx * dy * dz);
-    for (int c = 0; c < 6; ++c) out[(size_t)c * n + idx] = v[c] * kf;
-  }
+  const long long n = (long long)nx * ny * nz;
+  const long long idx = ((long long)k * ny + j) * nx + i;
+  const double kf = f / (4.0 * 3.14159265358979323846 * dx * dy * dz);
+  for (int c = 0; c < 6; ++c) out[(size_t)c * n + idx] = v[c] * kf;
 }
 
 __global__ void __launch_bounds__(256)
@@ -299,9 +329,9 @@ k_newell_far(double* __restrict__ out, int nx, int ny, int nz, double dx, double
   double tx[3], ty[3], tz[3], wx[3], wy[3], wz[3];
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    far_axis(rl.x[10 + q], rl.w[10 + q], dx, tx[q], wx[q]);
-    far_axis(rl.x[10 + q], rl.w[10 + q], dy, ty[q], wy[q]);
-    far_axis(rl.x[10 + q], rl.w[10 + q], dz, tz[q], wz[q]);
+    far_axis(rl.x[q], rl.w[q], dx, tx[q], wx[q]);
+    far_axis(rl.x[q], rl.w[q], dy, ty[q], wy[q]);
+    far_axis(rl.x[q], rl.w[q], dz, tz[q], wz[q]);
     tx[q] = (lane & 1) ? X - tx[q] : X + tx[q];
     ty[q] = (lane & 2) ? Y - ty[q] : Y + ty[q];
     tz[q] = (lane & 4) ? Z - tz[q] : Z + tz[q];
@@ -472,16 +502,18 @@ void launch_newell_octant(hipStream_t s, double* out, int nx, int ny, int nz, do
                        nx, ny, nz, dx, dy, dz, gr);
     return;
   }
-  // box of the offsets below 40 h
+  // boxes of the offsets below 6 h and below 40 h
   const double h = dx > dy ? (dx > dz ? dx : dz) : (dy > dz ? dy : dz);
-  auto ext = [&](int m, double d) {
-    const double e = 40.0 * h / d + 2.0;
+  auto ext = [&](double r, int m, double d) {
+    const double e = r * h / d + 2.0;
     return e < (double)m ? (int)e : m;
   };
-  const int bx = ext(nx, dx), by = ext(ny, dy), bz = ext(nz, dz);
+  const int cx = ext(6.0, nx, dx), cy = ext(6.0, ny, dy), cz = ext(6.0, nz, dz);
+  const int bx = ext(40.0, nx, dx), by = ext(40.0, ny, dy), bz = ext(40.0, nz, dz);
+  const int ncb = (int)(((long long)cx * cy * cz + 7) / 8);      // two offsets per wave
   const long long nb = (long long)bx * by * bz;
-  hipLaunchKernelGGL(k_newell_near, dim3((unsigned)((nb + 3) / 4)), dim3(256), 0, s, out, nx, ny,
-                     nz, bx, by, bz, dx, dy, dz, gr);
+  hipLaunchKernelGGL(k_newell_near, dim3((unsigned)(ncb + (nb + 3) / 4)), dim3(256), 0, s, out, nx,
+                     ny, nz, ncb, cx, cy, cz, bx, by, bz, dx, dy, dz, gr);
   if (bx < nx || by < ny || bz < nz ||
       (double)(nx - 1) * dx * (nx - 1) * dx + (double)(ny - 1) * dy * (ny - 1) * dy +
               (double)(nz - 1) * dz * (nz - 1) * dz >= 1599.0 * h * h)
