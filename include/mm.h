@@ -410,7 +410,11 @@ int mm_last_step(mm_ctx* ctx, int sample, mm_step_info* info);
  * 6 "y3_inv" (full 3-D path: forward y, z transform with tensor product,
  * inverse y), 7 "finish" (reduction of the per-block sums, stop rule, step
  * choice), 8 "reference" (the whole double-precision reference pass of the
- * mixed form's defect correction, one record per pass).
+ * mixed form's defect correction, one record per pass).  A double-precision
+ * film of up to 1024 cells that one workgroup holds runs as one launch per
+ * evaluation or per batch of up to poll_every iterations: its records come
+ * under "xf", the other passes have none (they serve its line-search runs).
+ * Timing changes neither what runs nor its results.
  * mm_kernel_bytes(ctx, sample, id, &bytes) gives that kernel's algorithmic
  * bytes per launch in a minimiser iteration (compulsory reads + writes). */
 int mm_profile(mm_ctx* ctx, int mask);

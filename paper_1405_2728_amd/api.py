@@ -293,7 +293,9 @@ class Context:
     # -- timing ---------------------------------------------------------------
     def profile(self, kernels=None):
         """Time the named kernels (None or [] stops; "all" times every
-        kernel) with HIP events."""
+        kernel) with HIP events.  A double-precision film that one workgroup
+        holds runs as one launch per evaluation or batch of iterations,
+        recorded under "xf"."""
         mask = 0
         if kernels == "all":
             mask = (1 << 30) - 1

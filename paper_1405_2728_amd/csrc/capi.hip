@@ -627,9 +627,10 @@ void enqueue_reference(mm_ctx* c, Sample& s, const double* m, const MinState* ms
 
 // Whether the sample runs in one workgroup (small.hip): double precision, a
 // thin film outside the wave FFT lengths (which batched sweeps share), no
-// line search; not while kernels are timed, which is per pass.
+// line search.  Timing does not decide it: a timed run has the bits of an
+// untimed one and times what such a run launches.
 bool small_ok(const mm_ctx* c, const Sample& s) {
-  return s.small && !c->ls.on && c->prof == 0;
+  return s.small && !c->ls.on;
 }
 
 // nit iterations on m (nit > 0), or one evaluation
@@ -642,6 +643,7 @@ void enqueue_small(mm_ctx* c, Sample& s, const double* m, const EvalOut& o, int 
   a.Han_out = o.Han;
   a.done = nit > 0 ? &s.st->done : o.done;
   const double scale = -s.Ms / ((double)s.M * (double)s.Py);
+  Timer t(c, KID_XF);   // the only launch of the batch or evaluation
   launch_small(c->stream, a, const_cast<double*>(m), as<double>(s.s), nit,
                nit > 0 ? s.st : o.st_fin, s.M, s.Py, (const double*)s.Tt, s.tstride, scale, s.twx,
                s.twy, o.Hd, s.Ms, s.V);
@@ -2490,6 +2492,12 @@ int mm_kernel_bytes(mm_ctx* c, int sample, int id, double* bytes) {
   const double bsp64 = s.path == PATH_3D ? (double)(s.M + 1) * s.Py * 3 * s.nz * 16.0 : 0.0;
   const double mid64 = thin ? 2 * spec64 + tens64 : 2 * spec64 + 4 * bsp64 + tens64;
   double b = 0;
+  if (small_ok(c, s)) {   // one launch: m, g, s in and out, the tensor
+    *bytes = id == KID_XF       ? 2 * N3 + 4 * G3 + tens + ku
+             : id == KID_UPDATE ? 2 * N3 + 2 * G3
+                                : 0.0;
+    return MM_OK;
+  }
   switch (id) {
     case KID_XF: b = 2 * N3 + 2 * G3 + spec + corr; break;   // m, g in; m, s out; spectrum out
     case KID_YZ: b = thin ? 2 * spec + tens : 0; break;   // spectrum in/out; tensor in

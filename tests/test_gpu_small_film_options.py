@@ -1,0 +1,64 @@
+"""Options that must not change what a small film computes.
+
+Double-precision films of up to 1024 cells run in one workgroup.  Timing the
+kernels leaves their fields, energies and runs the same bit for bit; the timer
+records the launches such a run makes, under "xf".
+"""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+GRIDS = [(20, 10, 1), (33, 16, 1), (32, 30, 1), (12, 7, 2)]
+D = (5e-9, 4e-9, 6e-9)
+H = np.array([3e4, -2e3, 1e3])
+
+
+def context(n, **options):
+    from paper_1405_2728_amd import Context
+    ctx = Context("fp64")
+    for k, v in options.items():
+        ctx.set_option(k, v)
+    ctx.set_geometry(0, *n, *D)
+    ctx.set_material(0, 8e5, 1.3e-11, 500.0, (1, 0.2, 0))
+    ctx.set_field(0, H)
+    return ctx
+
+
+def start(n):
+    return synth.uniform_with_noise((1, 0.3, 0), *n, 1e-2, np.random.default_rng(4))
+
+
+@pytest.mark.parametrize("n", GRIDS)
+def test_timing_leaves_the_run_and_times_its_launches(n):
+    m0 = start(n)
+    out = []
+    for timed in (False, True):
+        with context(n) as ctx:
+            if timed:
+                ctx.profile("all")
+            m = torch.tensor(m0, device="cuda")
+            h = ctx.heff(0, m)
+            e = ctx.energy(0, m)
+            r = ctx.minimize_to_tol(0, m, tol=0.0, max_iter=70)
+            part = torch.tensor(m0, device="cuda")
+            ctx.minimize_to_tol(0, part, tol=0.0, max_iter=37)
+            if timed:
+                ctx.profile(None)           # timing ends within the run
+            ctx.minimize_continue(0, part, tol=0.0, max_iter=70)
+            assert torch.equal(part, m)
+            out.append((h, e, r, m))
+            if timed:
+                prof = ctx.profile_read()
+                # field, energy, 71 evaluations in batches of 32, 38 in two
+                assert prof["xf"][1] == 2 + 3 + 2 and prof["xf"][0] > 0.0
+                assert sum(v[1] for k, v in prof.items() if k != "xf") == 0
+                b = ctx.kernel_bytes(0)
+                assert b["xf"] > 0 and b["yz_thin"] == b["xil"] == b["finish"] == 0
+    (h0, e0, r0, m1), (h1, e1, r1, m2) = out
+    assert torch.equal(h0, h1) and e0 == e1 and r0 == r1 and torch.equal(m1, m2)
