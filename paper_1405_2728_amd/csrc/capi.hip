@@ -626,11 +626,12 @@ void enqueue_reference(mm_ctx* c, Sample& s, const double* m, const MinState* ms
 }
 
 // Whether the sample runs in one workgroup (small.hip): double precision, a
-// thin film outside the wave FFT lengths (which batched sweeps share), no
-// line search.  Timing does not decide it: a timed run has the bits of an
-// untimed one and times what such a run launches.
-bool small_ok(const mm_ctx* c, const Sample& s) {
-  return s.small && !c->ls.on;
+// thin film outside the wave FFT lengths (which batched sweeps share); not
+// the iterations of a line-search run, whose trials the separate passes hold.
+// Timing does not decide it: a timed run has the bits of an untimed one and
+// times what such a run launches.
+bool small_ok(const mm_ctx* c, const Sample& s, bool iterate = true) {
+  return s.small && !(iterate && c->ls.on);
 }
 
 // nit iterations on m (nit > 0), or one evaluation
@@ -656,7 +657,7 @@ void enqueue_small(mm_ctx* c, Sample& s, const double* m, const EvalOut& o, int 
 // the previous iteration's finish over and this iteration's is left pending.
 void enqueue_eval(mm_ctx* c, Sample& s, const double* m, const EvalOut& o) {
   if (o.fuse_q <= 0) flush_finish(c, s);
-  if (small_ok(c, s)) {
+  if (small_ok(c, s, o.iterate)) {
     enqueue_small(c, s, m, o, o.iterate ? 1 : 0);
     return;
   }

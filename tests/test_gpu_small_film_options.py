@@ -1,8 +1,11 @@
 """Options that must not change what a small film computes.
 
 Double-precision films of up to 1024 cells run in one workgroup.  Timing the
-kernels leaves their fields, energies and runs the same bit for bit; the timer
-records the launches such a run makes, under "xf".
+kernels and turning the line search on (which concerns runs only) leave their
+fields, energies and, for timing, runs the same bit for bit; the timer records
+the launches such a run makes, under "xf".  Line-search runs, which take the
+separate passes at the film's own padded lengths, follow the oracle's iterates
+(1e-8, the bound of the other iterate tests).
 """
 
 import numpy as np
@@ -11,6 +14,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import synth
+from oracle import fields as ofields, minimizer as omin
 
 pytestmark = pytest.mark.gpu
 
@@ -62,3 +66,21 @@ def test_timing_leaves_the_run_and_times_its_launches(n):
                 assert b["xf"] > 0 and b["yz_thin"] == b["xil"] == b["finish"] == 0
     (h0, e0, r0, m1), (h1, e1, r1, m2) = out
     assert torch.equal(h0, h1) and e0 == e1 and r0 == r1 and torch.equal(m1, m2)
+
+
+@pytest.mark.parametrize("n", GRIDS)
+def test_line_search_option(n):
+    # a first step far too long: trials are rejected and shortened
+    m0 = synth.uniform_with_noise((1, 0.3, 0.1), *n, 0.2, np.random.default_rng(17))
+    tau0 = 3.0 / 8e5
+    m = torch.tensor(m0, device="cuda")
+    with context(n) as ctx:
+        h, e = ctx.heff(0, m), ctx.energy(0, m)
+    P = ofields.Problem(*n, *D, Ms=8e5, A=1.3e-11, Ku=500.0, u=(1, 0.2, 0), H_ext=H)
+    ref = omin.minimize_ls(P, m0, tol=0.0, max_iter=10, tau0=tau0)
+    assert ref["backtracks"] >= 1
+    with context(n, line_search=1, tau0=tau0) as ctx:
+        assert torch.equal(ctx.heff(0, m), h) and ctx.energy(0, m) == e
+        r = ctx.minimize_to_tol(0, m, tol=0.0, max_iter=10)
+        assert r["iters"] == 10 and r["heff_evals"] == ref["heff_evals"]
+        assert np.max(np.abs(m.cpu().numpy() - ref["m"])) < 1e-8
