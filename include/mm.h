@@ -327,7 +327,8 @@ int mm_mean(mm_ctx* ctx, int sample, const double* m, double* mavg);
  * timing; the variants compute the same bits),
  * "rows_per_block" (0 = automatic; otherwise that tile for every later
  * mm_set_geometry, which fails with MM_EINVAL where it is not valid: for
- * testing every tile), "yz_variant" (-1 = automatic; 0 or 1 that yz
+ * testing every tile; while it or yz_variant is forced, films that one
+ * workgroup holds take the separate passes too), "yz_variant" (-1 = automatic; 0 or 1 that yz
  * occupancy variant for every later mm_set_geometry, which fails with
  * MM_EINVAL where the grid has no such variant: for testing), "mixed_radix" (default 1, read by mm_set_geometry:
  * the padded x length is the smaller of the power of two >= 2 nx - 1 and
@@ -369,7 +370,8 @@ int mm_set_option(mm_ctx* ctx, const char* key, double value);
 
 /* Rows per block of the sample's fused x passes (host int output), as the
  * heuristic, the autotuner or the rows_per_block option chose it at
- * mm_set_geometry. */
+ * mm_set_geometry (of a film that one workgroup holds: for its line-search
+ * runs, which take the separate passes). */
 int mm_rows_per_block(mm_ctx* ctx, int sample, int* rows);
 
 /* Occupancy variant of the sample's thin-film yz pass (host int output: 0

@@ -127,7 +127,7 @@ struct mm_ctx {
   int path_pref = 0;            // 0 automatic, 1 thin-film, 2 full 3-D
   int refine = 1;               // single-precision form: defect correction on
   int autotune = 0;             // 1: time the x-pass tiles at mm_set_geometry
-  int rows_forced = 0;          // > 0: rows per block of the x passes (tests)
+  int rows_forced = 0;          // > 0: rows per block of the x passes (tests; small films then take them)
   int yz_forced = -1;           // >= 0: occupancy variant of the thin yz pass (tests)
   int mixed_radix = 1;          // 1: wave lengths 64 VL (VL = 3, 5, 6, 7) where shorter
   int concurrent_groups = 1;    // batched passes: launch groups on forked streams
@@ -1688,8 +1688,11 @@ int mm_set_geometry(mm_ctx* c, int sample, int nx, int ny, int nz, double dx, do
   if (!full && c->prec == MM_FP64 && yz_long_ok(nz, s.Py)) s.Py = pad_long(2 * ny - 1, 128, s.Py, mr);
   s.Pz = full ? pad_3d(nz) : 1;
   const bool sp = single(c);
+  // a forced tile or yz variant asks for the separate passes
+  const bool forced = c->rows_forced > 0 || c->yz_forced >= 0;
   int small_m = 0, small_p = 0;
-  s.small = !full && !sp && (s.M < 64 || s.Py < 64) && small_shape(nx, ny, nz, small_m, small_p);
+  s.small = !full && !sp && !forced && (s.M < 64 || s.Py < 64) &&
+            small_shape(nx, ny, nz, small_m, small_p);
   if (s.small) {
     s.M = small_m;
     s.Px = 2 * small_m;

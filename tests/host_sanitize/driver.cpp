@@ -209,6 +209,25 @@ void run_context(int prec) {
     int rows = 0;
     expect(mm_rows_per_block(ctx, s, &rows), MM_OK, "rows_per_block");
   }
+  step("short film on the LDS passes in either precision (forced tile)");
+  {
+    const double u[3] = {1, 0, 0}, f[3] = {-4e3, 1.5e3, 0.0};
+    double E = 0;
+    mm_min_result r;
+    expect(mm_set_option(ctx, "rows_per_block", 2), MM_OK, "option rows_per_block");
+    expect(mm_set_geometry(ctx, 1, shp[1].nx, shp[1].ny, shp[1].nz, 5e-9, 5e-9, 5e-9), MM_OK,
+           "set_geometry forced tile");
+    expect(mm_set_material(ctx, 1, 8e5, 1.3e-11, 500.0, u, nullptr), MM_OK, "set_material");
+    expect(mm_set_field(ctx, 1, f), MM_OK, "set_field");
+    expect(mm_heff(ctx, 1, m[1]->p, H[1]->p), MM_OK, "heff forced tile");
+    expect(mm_energy(ctx, 1, m[1]->p, &E, nullptr), MM_OK, "energy forced tile");
+    expect_ok_or(mm_minimize_to_tol(ctx, 1, m[1]->p, 1e-6, 3000, &r), MM_NOT_CONVERGED,
+                 "to_tol forced tile");
+    expect_ok_or(mm_hysteresis_sweep(ctx, mp, fields.data(), F, 1e-5, 2000, mavg.data(),
+                                     iters.data()),
+                 MM_NOT_CONVERGED, "sweep forced tile");
+    expect(mm_set_option(ctx, "rows_per_block", 0), MM_OK, "option rows_per_block off");
+  }
   step("destroy");
   for (auto* d : m) delete d;
   for (auto* d : H) delete d;
