@@ -332,10 +332,10 @@ int mm_mean(mm_ctx* ctx, int sample, const double* m, double* mavg);
  * occupancy variant for every later mm_set_geometry, which fails with
  * MM_EINVAL where the grid has no such variant: for testing), "mixed_radix" (default 1, read by mm_set_geometry:
  * the padded x length is the smaller of the power of two >= 2 nx - 1 and
- * the multiple of 128 >= 2 nx - 1 (up to 1024; in double precision on thin
- * films also 1280, 1536, 1792 and 2048), the thin-film y length the smaller
- * of the power of two >= 2 ny - 1 and the multiple of 64 (up to 512; in
- * double precision up to three layers also 640, 768, 896 and 1024), so that
+ * the multiple of 128 >= 2 nx - 1 (up to 1024; in double precision, on both
+ * demag paths, also 1280, 1536, 1792 and 2048), the thin-film y length the
+ * smaller of the power of two >= 2 ny - 1 and the multiple of 64 (up to 512;
+ * in double precision up to three layers also 640, 768, 896 and 1024), so that
  * transforms of 64 VL points with VL = 3, 5, 6, 7 (10, 12, 14) take the place
  * of the next power of two; 0 keeps powers of two; double-precision films of
  * up to 1024 cells that one workgroup holds have their own lengths, 64 or 128
