@@ -190,10 +190,14 @@ k_cg_direction(const double* __restrict__ m, const double* __restrict__ r,
 // loads are in flight.  A one-block kernel costs its launch, a boundary and a
 // round trip whatever it sums (about 3 us); a block's own sum costs nb / 256
 // loads per thread, so this form serves grids of up to kCgOwnSums partial
-// sums.  Nothing that a block reads is written in the same kernel: the two
-// sums have their own buffers, |r|^2 alternates between two places, and a
-// breakdown is noted in `bad` and becomes `done` one kernel later.
-// 200 x 100 x 2, 8 -> 6 kernels per iteration: solve and gradients 2237 -> 1865 us.
+// sums.  Per solve of 20 to 26 iterations, 8 -> 6 kernels each: 512 x 256 x 1
+// and 64 x 64 x 32 (512 sums) 1230 -> 1140 and 2090 -> 1997 us; beyond the
+// limit the gain shrinks, 512 x 512 x 1 and 64^3 (1024) 1629 -> 1533 and 3167
+// -> 3092, and ends at 1000 x 500 x 1 and 128 x 64 x 64 (about 2000), 2592 ->
+// 2601 and 4642 -> 4671.  Nothing that a block reads is written in the same
+// kernel: the two sums have their own buffers, |r|^2 alternates between two
+// places, and a breakdown is noted in `bad` and becomes `done` one kernel
+// later.  200 x 100 x 2: solve and gradients 2237 -> 1865 us.
 constexpr int kCgOwnSums = 512;
 
 // the block's copy of sum(partials), in every thread

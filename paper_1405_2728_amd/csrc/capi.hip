@@ -969,8 +969,8 @@ int build_batch(mm_ctx* c, double* const* m, BatchPlan& P, const std::vector<cha
                              : y3_blocks(d[i].nz, d[i].Py, d[i].M, !sp);
       for (int blk = 0; blk < nb; ++blk) v.push_back({i, blk});
       const int len = st == 1 ? d[i].Pz : d[i].Py;
-      L.lds = std::max(L.lds, w3_block_lds(sp, st - 1, len, !sp));
-      L.lds_ref = std::max(L.lds_ref, w3_block_lds(false, st - 1, len, false));
+      L.lds = std::max(L.lds, w3_block_lds(sp, len, !sp));
+      L.lds_ref = std::max(L.lds_ref, w3_block_lds(false, len, false));
     }
     if (v.empty()) continue;
     xcd_order(v);

@@ -447,7 +447,8 @@ k_z3(cx<T>* __restrict__ B, int nz, int Py, const T* __restrict__ T3, int rstrid
 // XCD-ordered table (persist_loop), a branch on the item's length.
 static_assert(kY3Waves == kZ3Waves, "the 3-D stages share one block size");
 
-// PACK: the z stage packs its short pencils (double-precision contexts).
+// PACK: packed planes and pencils in all three stages (double-precision
+// contexts).
 template <typename T, int VL, bool PACK>
 __device__ __forceinline__ void w3_item(int stage, const BatchDesc& d, int L) {
   constexpr bool HALF = k3dHalf;
@@ -622,7 +623,7 @@ static size_t w3_lds() {
   return (size_t)kY3Waves * wfft_buf<VL, HALF>() * sizeof(cx<T>);
 }
 
-size_t w3_block_lds(bool single, int stage, int P, bool pack) {
+size_t w3_block_lds(bool single, int P, bool pack) {
   if (pack) return pack3_lds(P);
   switch (P) {
     case 64: return single ? w3_lds<float, 1>() : w3_lds<double, 1>();

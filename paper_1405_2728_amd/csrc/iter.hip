@@ -358,8 +358,10 @@ __device__ __forceinline__ void xf_w_body(double* __restrict__ m, const T* __res
     };
     if constexpr (!FUSE) {
       // the cell code written out in the loop: through the lambda the
-      // compiler holds this pass at 134 VGPRs instead of 128 (3 waves per
-      // SIMD instead of 4)
+      // persistent single-precision form of one row takes 134 VGPRs instead
+      // of 128 (3 waves per SIMD instead of 4), the persistent forms of
+      // several rows 159 and 165 instead of 141 and 147; the per-sample forms
+      // keep 4 waves either way
       const bool upd = pend != 0 && done == 0 && mcopy == nullptr;
       const bool ls_upd = upd && ls != 0;
       for (int base = first; base < total; base += U * nthr) {

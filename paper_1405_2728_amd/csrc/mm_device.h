@@ -396,10 +396,13 @@ __device__ __forceinline__ double dpp0_f64(double v) {
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-// Wave total in lane 63: an inclusive scan within each row of 16 lanes
-// (row_shr 1, 2, 4, 8: lane 15 of a row holds the row's total), then row 0's
-// total into row 1 and row 2's into row 3 (row_bcast 15), then lane 31's
-// into rows 2 and 3 (row_bcast 31).  No LDS traffic.
+// Wave total in lane 63 (the other lanes are left with partial sums): an
+// inclusive scan within each row of 16 lanes (row_shr 1, 2, 4, 8: lane 15 of a
+// row holds the row's total), then the last lane of each row added to the
+// next row (row_bcast 15: lanes 31 and 63 hold two rows' total), then lane
+// 31's added to rows 2 and 3 (row_bcast 31).  Every row takes part in each
+// step, so that no target register has to be cleared; wave_max masks the rows
+// that need none.  No LDS traffic.
 __device__ __forceinline__ double wave_sum(double v) {
   v += dpp0_f64<0x111>(v);
   v += dpp0_f64<0x112>(v);

@@ -240,7 +240,7 @@ void launch_x_persistent(hipStream_t s, bool inverse, const BatchDesc* descs,
 // the tensor product, +1 inverse y; items = (sample, block of the stage's
 // per-sample grid: y3_blocks for y, z3_blocks for z)
 int w3_persistent_grid(bool single, int stage, size_t lds, bool pack);
-size_t w3_block_lds(bool single, int stage, int P, bool pack);
+size_t w3_block_lds(bool single, int P, bool pack);
 int y3_blocks(int nz, int Py, int M, bool pack);
 int z3_blocks(int Py, int Pz, int M, bool pack);
 template <typename T>

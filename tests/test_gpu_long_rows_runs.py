@@ -96,3 +96,23 @@ def test_the_same_run_bit_for_bit(n):
         ctx.state_load(0, blob)
         rc = ctx.minimize_continue(0, m, tol=0.0, max_iter=K)
         assert torch.equal(m, ref) and rc == r
+
+
+@pytest.mark.parametrize("n", [(520, 30, 1), (1000, 20, 2)])
+def test_a_bounded_wait_that_gives_up_is_reported(n):
+    """Blocks told to give up at once (fin_spin 0) end the run with MM_ESTATE;
+    the context runs as before afterwards."""
+    from paper_1405_2728_amd import MMError
+    m0 = synth.uniform_with_noise((1, 0.3, 0.1), *n, 0.1, np.random.default_rng(23))
+    with context(n) as ctx:
+        ref = torch.tensor(m0, device="cuda")
+        ctx.minimize_to_tol(0, ref, tol=0.0, max_iter=20)
+        ctx.set_option("fin_spin", 0)
+        m = torch.tensor(m0, device="cuda")
+        with pytest.raises(MMError) as e:
+            ctx.minimize_to_tol(0, m, tol=0.0, max_iter=20)
+        assert e.value.code == -5
+        ctx.set_option("fin_spin", 1 << 22)
+        m = torch.tensor(m0, device="cuda")
+        ctx.minimize_to_tol(0, m, tol=0.0, max_iter=20)
+        assert torch.equal(m, ref)
