@@ -304,7 +304,8 @@ int mm_mean(mm_ctx* ctx, int sample, const double* m, double* mavg);
  * non-null stream: mm_minimize_to_tol and mm_hysteresis_sweep replay each
  * batch of poll_every iterations after the first as one captured HIP graph;
  * mm_minimize_to_tol keeps its graph per sample while m, poll_every, the
- * correction and the material stay the same; not while kernels are timed), "demag_path" (0 = automatic: thin-film path for nz <= 4, full 3-D
+ * correction and the material stay the same; not while kernels are timed, nor
+ * for films that one workgroup holds, whose batch is one launch), "demag_path" (0 = automatic: thin-film path for nz <= 4, full 3-D
  * path otherwise; 1 = thin-film path only; 2 = full 3-D path also for
  * nz <= 4; read by mm_set_geometry), "refine" (mixed form, default 1:
  * defect correction of the minimiser iterations.  Every poll_every

@@ -220,11 +220,14 @@ __device__ __forceinline__ void z3_body(cx<T>* __restrict__ B, int nz, int Py,
 // (double-precision contexts).  The
 // 8-point stages of a 64 VL-point transform use 8 VL lanes, so one pencil of
 // less than 512 points per wave leaves lanes idle in most of the work; 8 / VL
-// packed pencils keep all 64 busy.  The pass is bound by its instructions
-// (split into groups of kx planes whose B stays in the memory-side cache, it
-// took the same time), so the three components also take each stage together
-// and share the twiddle loads (70 instead of 96 vector memory instructions a
-// wave at 256 points) and their address arithmetic.
+// packed pencils keep all 64 busy.  The pass is not bound by memory (split into
+// groups of kx planes whose B stays in the memory-side cache, it took the same
+// time; 128^3 moves 526 MB in 164 us, 3.2 TB/s of a copy's 5.2) but by the
+// chain of a wave: 2.4 resident waves per SIMD keep the VALU busy a quarter of
+// the time (one pencil per wave: 36%) and wait for memory or LDS a third of
+// theirs.  So the three components also take each stage together, which gives
+// a wave independent work, and share the twiddle loads (70 instead of 96
+// vector memory instructions a wave at 256 points) and address arithmetic.
 // One pencil, component by component -> packed, component by component ->
 // packed, together: 100 x 75 x 20 (64 points) 111 -> 35 -> 36 us, 64^3 (128)
 // 39 -> 29 -> 30, 200 x 200 x 40 (128) 516 -> 335 -> 253, 128^3 (256) 206 ->
@@ -325,7 +328,8 @@ k_z3_pk(cx<double>* __restrict__ B, int nz, int Py, const double* __restrict__ T
 // (48 bytes each) in a piece.  One plane, component by component -> packed,
 // forward and inverse: 128^3 (256 points) 98 and 94 -> 84 and 77 us (304 MB
 // each: 3.6 and 3.9 TB/s), 48 x 48 x 140 (128) 31 and 27 -> 28 and 22,
-// 200 x 200 x 40 (512, one plane) 114 and 118 -> 114 and 104.
+// 200 x 200 x 40 (512, one plane) 114 and 118 -> 114 and 104.  What is left is
+// memory: two thirds of a wave's time is waiting, the VALU 11 to 13% busy.
 template <int VL>
 __device__ __forceinline__ void y3_fwd_pk_body(const cx<double>* __restrict__ A,
                                                cx<double>* __restrict__ B, int nz, int ny,

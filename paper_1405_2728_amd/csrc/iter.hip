@@ -256,13 +256,16 @@ __device__ __forceinline__ double fin_wait(const FinFuse& fz) {
 // Body of the forward x pass for logical block L (rows z, y0 .. y0+R-1).
 // FUSE: the pass takes the previous iteration's finish over (fz.st set).
 // RC: the rows per block where the kernel is compiled for them (1), else 0.
-// Both x passes are bound by the instructions a wave issues, not by memory
-// (issuing a cell's loads ahead of the spectrum's made the inverse pass 10 to
-// 35% slower), and with R at run time a third of them were divisions by 3 R
-// and nx and the 64-bit addresses of every optional output.  With one row a
-// thread keeps its place in the chunks, takes its cells from constants
-// (nx <= M: one round) and addresses them by 32-bit offsets: inverse pass at
-// M = 128 2113 -> 1279 instructions, forward 1858 -> 904.  Forward and
+// With R at run time both x passes were bound by the instructions a wave issues,
+// not by memory (128^3: inverse pass with the VALU busy 76% of the time;
+// issuing a cell's loads ahead of the spectrum's made it 10 to 35% slower), and
+// a third of them were divisions by 3 R and nx and the 64-bit addresses of
+// every optional output.  With one row a thread keeps its place in the chunks,
+// takes its cells from constants (nx <= M: one round) and addresses them by
+// 32-bit offsets: inverse pass at M = 128 2113 -> 1279 instructions, forward
+// 1858 -> 904; VALU busy 49% and 39%, 2.7 and 3.5 TB/s of a copy's 5.2: what
+// bounds them now is a block's chain of phases between its barriers, at 3.1
+// and 3.5 waves per SIMD (film, 800 blocks: 1.6, VALU busy a quarter).  Forward and
 // inverse: 128^3 90 and 124 -> 80 and 109 us, 400 x 200 x 4 21.9 and 22.0 ->
 // 20.7 and 20.0, mixed 20.8 and 21.6 -> 19.0 and 20.7, 200 x 100 x 2 13.8 and
 // 11.0 -> 12.5 and 10.0.

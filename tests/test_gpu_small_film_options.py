@@ -84,3 +84,19 @@ def test_line_search_option(n):
         r = ctx.minimize_to_tol(0, m, tol=0.0, max_iter=10)
         assert r["iters"] == 10 and r["heff_evals"] == ref["heff_evals"]
         assert np.max(np.abs(m.cpu().numpy() - ref["m"])) < 1e-8
+
+
+@pytest.mark.parametrize("n", GRIDS)
+def test_checkpoint_continues_bit_for_bit(n):
+    m0 = start(n)
+    with context(n) as ctx:
+        full = torch.tensor(m0, device="cuda")
+        r = ctx.minimize_to_tol(0, full, tol=0.0, max_iter=70)
+    with context(n) as ctx:
+        m = torch.tensor(m0, device="cuda")
+        ctx.minimize_to_tol(0, m, tol=0.0, max_iter=29)
+        blob = ctx.state_save(0)
+    with context(n) as ctx:
+        ctx.state_load(0, blob)
+        c = ctx.minimize_continue(0, m, tol=0.0, max_iter=70)
+        assert torch.equal(m, full) and c == r
