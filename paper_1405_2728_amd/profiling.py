@@ -155,7 +155,7 @@ def cmd_traffic(a):
         wb = wr.get(k, 0.0) * 1024.0 * f_write
         kernels[k] = {"fetch_bytes": fb, "write_bytes": wb, "bytes_per_launch": fb + wb}
     # bench.py looks kernels up by the library's timing names
-    alias = {"k_xf_w": "xf", "k_xf_wr": "xf", "k_xf_long": "xf", "k_xf": "xf",
+    alias = {"k_xf_w": "xf", "k_xf_wr": "xf", "k_xf_long": "xf", "k_xf": "xf", "k_small": "xf",
              "k_yz_wave": "yz_thin", "k_yz_long": "yz_thin", "k_yz_thin": "yz_thin",
              "k_xil_w": "xil", "k_xil_wr": "xil", "k_xil_long": "xil", "k_xil": "xil",
              "k_update": "update", "k_y3_fwd": "y3_fwd", "k_y3_fwd_pk": "y3_fwd",
